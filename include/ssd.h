@@ -96,7 +96,8 @@ typedef struct {
     int64_t headdim;     /* P                                        */
     int64_t dstate;      /* N                                        */
     int64_t ngroups;     /* G, divides H                             */
-    int64_t chunk_size;  /* Q, the block length of the decomposition */
+    int64_t chunk_size;  /* Q, the block length of the decomposition (the result does
+                            not depend on it; the fused kernels use 256)      */
     int64_t nseq;        /* number of sequences; read only when seq_idx != NULL */
     int32_t dtype;       /* ssd_dtype of x, dt, B, C, y              */
 } ssd_problem;
@@ -105,11 +106,14 @@ typedef struct {
  * chunk states, the packed row's chunk table).  The size covers calls with and
  * without seq_idx; with batch 1 it depends on prob->nseq, so size it with the
  * nseq the call will pass.  It is the size of the kernels the call will run:
- * at the shapes of the fused kernels (bf16, headdim 64, dstate 64/128/256,
+ * at the fused kernels' own shapes (bf16, headdim 64, dstate 64/128/256,
  * chunk 256) a fraction of the general kernels' (which keep every chunk
  * state), so a test setting that forces the general path (ssd_set_tuning)
- * must be made before the size is asked.  A workspace too small for the path
- * a call takes fails with SSD_ERR_WORKSPACE, never overruns.  Returns SSD_OK
+ * must be made before the size is asked.  At their other shapes (bf16, those
+ * dstates, headdim 64 with a shorter chunk or headdim 128) it covers both; a
+ * call there runs on the general kernels where x, B, C or y is not 16-byte
+ * aligned or the workspace holds only their layout.  A workspace too small for
+ * the path a call takes fails with SSD_ERR_WORKSPACE, never overruns.  Returns SSD_OK
  * and writes *bytes, or a validation error. */
 int ssd_workspace_bytes(const ssd_problem* prob, size_t* bytes);
 
@@ -142,7 +146,7 @@ int ssd_forward_timed(const ssd_problem* prob,
  * offsets instead of the device seq_idx: seq_starts (host memory) holds nseq +
  * 1 token offsets, seq_starts[0] = 0, strictly increasing, seq_starts[nseq] =
  * seqlen (else SSD_ERR_BAD_SHAPE); token t belongs to sequence s when
- * seq_starts[s] <= t < seq_starts[s + 1].  At the fused kernels' shapes and
+ * seq_starts[s] <= t < seq_starts[s + 1].  At the fused kernels' shapes (above) and
  * up to 511 sequences the offsets are handed to the device by value and the
  * row runs as one launch, as ssd_forward with seq_idx does; otherwise each
  * sequence runs as a problem of its own on its slice of the packed tensors.

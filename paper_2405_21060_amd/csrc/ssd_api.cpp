@@ -156,6 +156,51 @@ bool fused_packed_ok(const ssd_problem* prob)
     return prob->batch == 1 && prob->nseq >= 1 && prob->nseq <= prob->seqlen && prob->seqlen <= INT32_MAX;
 }
 
+bool aligned16(const void* p) { return reinterpret_cast<uintptr_t>(p) % 16 == 0; }
+
+// Layout of the fused kernels for a call: their heads of 64 features and
+// chunks of 256 tokens (nseq > 0: one packed row of nseq sequences).
+ssd::FusedLayout fused_plan(const ssd::Shape& s, int64_t nseq)
+{
+    return ssd::fused_layout(s.b, s.T, s.H * (s.P / ssd::kFusedP), s.N, s.G,
+                             (s.T + ssd::kFusedQ - 1) / ssd::kFusedQ, nseq);
+}
+
+bool fused_shape(const ssd::Shape& s)
+{
+    return ssd::tuning(ssd::kTuneForceGeneral) != 1 && ssd::fused_supported(s.H, s.P, s.N, s.bf16);
+}
+
+// The fused kernels' own shape (headdim 64, chunks of 256): always theirs.
+// Their other shapes (headdim 128, shorter chunks) fall back to the general
+// kernels where an operand is not 16-byte aligned or the workspace holds only
+// the general layout (fixed scratch sized for it): what those took stays taken.
+// Elsewhere the fused ones are the faster at every size (2 x 4096 tokens, 40
+// heads of 128, N 128: 115 us against 2705 on the general kernels as they were,
+// about 400 as they are).
+bool fused_only(const ssd::Shape& s) { return fused_shape(s) && s.P == ssd::kFusedP && s.Q == ssd::kFusedQ; }
+
+size_t general_bytes(const ssd::Shape& s)
+{
+    return ssd::workspace_layout(s.b, s.H, s.P, s.N, s.G, s.Q, s.nC).total;
+}
+
+// Workspace of a forward: the least a call can run on, and what it runs best
+// on (with batch 1, with or without a packed row of prob->nseq sequences).
+void forward_needs(const ssd_problem* prob, const ssd::Shape& s, size_t* least, size_t* best)
+{
+    const size_t general = general_bytes(s);
+    *least = *best = general;
+    if (!fused_shape(s)) return;
+    size_t fused = fused_plan(s, 0).total;
+    if (fused_packed_ok(prob))   // a packed row of prob->nseq sequences (when seq_idx is passed) needs its chunk table
+        fused = std::max(fused, fused_plan(s, prob->nseq).total);
+    else if (prob->batch == 1 && prob->nseq >= 1 && prob->nseq <= prob->seqlen)
+        fused = std::max(fused, general);   // a packed row the fused kernels cannot index
+    *best = fused_only(s) ? fused : std::max(fused, general);
+    if (fused_only(s)) *least = fused;
+}
+
 }  // namespace
 
 extern "C" int ssd_workspace_bytes(const ssd_problem* prob, size_t* bytes)
@@ -164,21 +209,9 @@ extern "C" int ssd_workspace_bytes(const ssd_problem* prob, size_t* bytes)
     ssd::Shape s;
     const int rc = ssd::validate(prob, /*has_seq_idx=*/false, &s);  // size does not depend on it
     if (rc != SSD_OK) return rc;
-    // The size of the path the forward will take: the fused kernels' layout
-    // where they apply (a fraction of the general layout, which holds every
-    // chunk state), else the general one.  Forcing the general path through
-    // ssd_set_tuning changes the answer.
-    const size_t general = ssd::workspace_layout(s.b, s.H, s.P, s.N, s.G, s.Q, s.nC).total;
-    size_t need = general;
-    if (ssd::tuning(ssd::kTuneForceGeneral) != 1 && ssd::fused_supported(s.P, s.N, s.Q, s.bf16)) {
-        need = ssd::fused_layout(s.b, s.T, s.H, s.N, s.G, s.nC, 0).total;
-        // a packed row of prob->nseq sequences (when seq_idx is passed) needs its chunk table
-        if (fused_packed_ok(prob))
-            need = std::max(need, ssd::fused_layout(1, s.T, s.H, s.N, s.G, s.nC, prob->nseq).total);
-        else if (prob->batch == 1 && prob->nseq >= 1 && prob->nseq <= prob->seqlen)
-            need = std::max(need, general);   // a packed row the fused kernels cannot index
-    }
-    *bytes = need;
+    // Forcing the general path through ssd_set_tuning changes the answer.
+    size_t least = 0;
+    forward_needs(prob, s, &least, bytes);
     return SSD_OK;
 }
 
@@ -189,8 +222,6 @@ extern "C" int ssd_block_workspace_bytes(const ssd_problem* prob, const ssd_bloc
 }
 
 namespace {
-
-bool aligned16(const void* p) { return reinterpret_cast<uintptr_t>(p) % 16 == 0; }
 
 // Block options against the shape; fills the dt parameterisation.
 int validate_block(const ssd_block_opts* o, const ssd::Shape& s, const void* y, ssd::DtTransform* dtx)
@@ -229,12 +260,12 @@ int forward_impl(const ssd_problem* prob, const ssd_block_opts* opts, const void
     if (!x || !dt || !A_log || !B || !C || !y) return SSD_ERR_NULL_ARG;
     ssd::DtTransform dtx;
     if (opts && (rc = validate_block(opts, s, y, &dtx)) != SSD_OK) return rc;
-    size_t need = 0;
+    size_t least = 0, best = 0;
     if (arg_starts)
-        need = ssd::fused_layout(1, s.T, s.H, s.N, s.G, s.nC, s.nseq).total;
-    else if (ssd_workspace_bytes(prob, &need) != SSD_OK)
-        return SSD_ERR_WORKSPACE;
-    if (!workspace || workspace_bytes < need) return SSD_ERR_WORKSPACE;
+        least = fused_plan(s, s.nseq).total;
+    else
+        forward_needs(prob, s, &least, &best);
+    if (!workspace || workspace_bytes < least) return SSD_ERR_WORKSPACE;
     // output side of the block: gate and grouped normalisation
     ssd::GateNormParams gn;
     gn.rows = s.b * s.T;
@@ -245,18 +276,21 @@ int forward_impl(const ssd_problem* prob, const ssd_block_opts* opts, const void
     gn.weight = opts ? opts->norm_weight : nullptr;
     gn.eps = opts ? opts->norm_eps : 0.f;
     const bool post = gn.z || gn.group > 0;
-    const bool force_unfused = ssd::tuning(ssd::kTuneForceGeneral) == 1;
+    bool fused = arg_starts || (fused_shape(s) && (!seq_idx || fused_packed_ok(prob)));
+    if (fused && !arg_starts && !fused_only(s))
+        fused = workspace_bytes >= fused_plan(s, seq_idx ? s.nseq : 0).total && aligned16(x) && aligned16(B) &&
+                aligned16(C) && aligned16(y);   // (z: checked with the block's options)
     // status word: in the workspace's header unless the caller keeps it elsewhere
     if (!status) status = static_cast<int*>(workspace);
-    if (arg_starts ||
-        (!force_unfused && ssd::fused_supported(s.P, s.N, s.Q, s.bf16) && (!seq_idx || fused_packed_ok(prob)))) {
+    if (fused) {
         const int64_t nseq = seq_idx || arg_starts ? s.nseq : 0;
-        const ssd::FusedLayout fw = ssd::fused_layout(s.b, s.T, s.H, s.N, s.G, s.nC, nseq);
+        const ssd::FusedLayout fw = fused_plan(s, nseq);
         ssd::FusedParams f;
         f.b = s.b;
         f.T = s.T;
-        f.H = s.H;
-        f.P = s.P;
+        f.H = s.H * (s.P / ssd::kFusedP);
+        f.head128 = s.P == 2 * ssd::kFusedP ? 1 : 0;
+        f.P = ssd::kFusedP;
         f.N = s.N;
         f.G = s.G;
         f.nC = fw.nC;
@@ -264,7 +298,7 @@ int forward_impl(const ssd_problem* prob, const ssd_block_opts* opts, const void
         if (hipGetDevice(&dev) != hipSuccess ||
             hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
             return SSD_ERR_LAUNCH;
-        f.HG = ssd::heads_per_workgroup(s.H / s.G, fw.nC * s.b * s.G, cus);
+        f.HG = ssd::heads_per_workgroup(f.H / s.G, fw.nC * s.b * s.G, cus);
         // The chain of state passing takes about nC chunk steps one after the
         // other (a step: a chunk's wait, state load, combine and publish), the
         // work about rounds x heads per item head-times.  Where the chain is
@@ -280,7 +314,7 @@ int forward_impl(const ssd_problem* prob, const ssd_block_opts* opts, const void
         // table entries / sequences chunks long (the longest is unknown here
         // when the boundaries are on the device).
         const bool by_depth = nseq > 1 && ssd::tuning(ssd::kTunePackedOrder) != 1;
-        const int64_t items = fw.nC * s.b * (s.H / f.HG);
+        const int64_t items = fw.nC * s.b * (f.H / f.HG);
         const int64_t rounds = (items + cus - 1) / cus;
         const int64_t chain = by_depth ? (fw.nC + nseq - 1) / nseq : fw.nC;
         f.early_flag = chain >= 2 * rounds * f.HG ? 1 : 0;
@@ -335,9 +369,9 @@ int forward_impl(const ssd_problem* prob, const ssd_block_opts* opts, const void
         // the chunk kernel).  The separate_block_post tuning leaves gate and
         // normalisation to that pass in every case.
         const bool separate = ssd::tuning(ssd::kTuneSeparatePost) == 1;
-        if (post && !separate && (gn.group == 0 || gn.group == s.P)) {
+        if (post && !separate && (gn.group == 0 || gn.group == ssd::kFusedP)) {
             f.z = gn.z;
-            if (gn.group == s.P) {
+            if (gn.group == ssd::kFusedP) {
                 f.norm_head = 1;
                 f.norm_weight = gn.weight;
                 f.norm_eps = gn.eps;
@@ -710,7 +744,7 @@ struct BlockBwdLayout {
 BlockMode block_mode(const ssd::Shape& s)
 {
     if (!s.bf16) return kF32;
-    if (ssd::tuning(ssd::kTuneForceGeneral) != 1 && ssd::fused_supported(s.P, s.N, 256, true) &&
+    if (ssd::tuning(ssd::kTuneForceGeneral) != 1 && ssd::fused_supported(s.H, s.P, s.N, true) &&
         ssd::bwd_fast_supported(true, s.P, s.N))
         return kMatrix;
     return kWidened;
@@ -1131,10 +1165,19 @@ bool varlen_one_launch(const ssd_problem* prob)
     if (ssd::tuning(ssd::kTuneForceGeneral) == 1 || ssd::tuning(ssd::kTuneVarlenPerSequence) == 1) return false;
     ssd::Shape s;
     if (ssd::validate(prob, true, &s) != SSD_OK) return false;
-    return ssd::fused_supported(s.P, s.N, s.Q, s.bf16) && fused_packed_ok(prob) && prob->nseq <= ssd::kArgSeqs;
+    return fused_shape(s) && fused_packed_ok(prob) && prob->nseq <= ssd::kArgSeqs;
 }
 
-int fwd_varlen_plan(const ssd_problem* prob, const int64_t* seq_starts, size_t* bytes)
+// Workspace of one launch over the row (0 where that is not possible), and of
+// one call per sequence: the least it runs on, and what it runs best on.
+struct VarlenNeeds {
+    size_t one = 0, per_least = 0, per_best = 0;
+    bool only_one = false;   // the fused kernels' own shape: one launch, or an error
+    size_t least() const { return only_one ? one : per_least; }
+    size_t best() const { return only_one ? one : std::max(one, per_best); }
+};
+
+int fwd_varlen_plan(const ssd_problem* prob, const int64_t* seq_starts, VarlenNeeds* n)
 {
     if (!prob || !seq_starts) return SSD_ERR_NULL_ARG;
     if (prob->batch != 1) return SSD_ERR_SEQIDX_BATCH;
@@ -1146,19 +1189,21 @@ int fwd_varlen_plan(const ssd_problem* prob, const int64_t* seq_starts, size_t* 
         ssd::Shape sh;
         const int rc = ssd::validate(prob, true, &sh);
         if (rc != SSD_OK) return rc;
-        *bytes = ssd::fused_layout(1, sh.T, sh.H, sh.N, sh.G, sh.nC, sh.nseq).total;
-        return SSD_OK;
+        n->one = fused_plan(sh, sh.nseq).total;
+        n->only_one = fused_only(sh);
+        if (n->only_one) return SSD_OK;
     }
-    size_t need = 0;
     for (int64_t s = 0; s < prob->nseq; ++s) {
         ssd_problem q = *prob;
         q.seqlen = seq_starts[s + 1] - seq_starts[s];
-        size_t b = 0;
-        const int rc = ssd_workspace_bytes(&q, &b);
+        ssd::Shape sh;
+        const int rc = ssd::validate(&q, false, &sh);
         if (rc != SSD_OK) return rc;
-        if (b > need) need = b;
+        size_t least = 0, best = 0;
+        forward_needs(&q, sh, &least, &best);
+        n->per_least = std::max(n->per_least, least);
+        n->per_best = std::max(n->per_best, best);
     }
-    *bytes = need;
     return SSD_OK;
 }
 
@@ -1168,7 +1213,10 @@ extern "C" int ssd_forward_varlen_workspace_bytes(const ssd_problem* prob, const
                                                   size_t* bytes)
 {
     if (!bytes) return SSD_ERR_NULL_ARG;
-    return fwd_varlen_plan(prob, seq_starts, bytes);
+    VarlenNeeds n;
+    const int rc = fwd_varlen_plan(prob, seq_starts, &n);
+    if (rc == SSD_OK) *bytes = n.best();
+    return rc;
 }
 
 extern "C" int ssd_forward_varlen(const ssd_problem* prob, const int64_t* seq_starts, const void* x,
@@ -1176,14 +1224,15 @@ extern "C" int ssd_forward_varlen(const ssd_problem* prob, const int64_t* seq_st
                                   const float* D, const float* initial_states, void* y, float* final_states,
                                   void* workspace, size_t workspace_bytes, void* stream)
 {
-    size_t need = 0;
-    int rc = fwd_varlen_plan(prob, seq_starts, &need);
+    VarlenNeeds n;
+    int rc = fwd_varlen_plan(prob, seq_starts, &n);
     if (rc != SSD_OK) return rc;
     ssd::Shape s;
     if ((rc = ssd::validate(prob, true, &s)) != SSD_OK) return rc;
     if (!x || !dt || !A_log || !B || !C || !y) return SSD_ERR_NULL_ARG;
-    if (!workspace || workspace_bytes < need) return SSD_ERR_WORKSPACE;
-    if (varlen_one_launch(prob)) {
+    if (!workspace || workspace_bytes < n.least()) return SSD_ERR_WORKSPACE;
+    if (n.one > 0 && (n.only_one || (workspace_bytes >= n.one && aligned16(x) && aligned16(B) && aligned16(C) &&
+                                     aligned16(y)))) {
         ssd::SeqStartsArg a;
         a.n = static_cast<int>(prob->nseq);
         for (int64_t q = 0; q <= prob->nseq; ++q) a.v[q] = static_cast<int>(seq_starts[q]);
@@ -1306,10 +1355,12 @@ extern "C" int ssd_forward_noalloc(const ssd_problem* prob, const void* x, const
                                    const int32_t* seq_idx, void* y, float* final_states, int32_t* status,
                                    void* stream)
 {
-    size_t need = 0;
-    int rc = ssd_workspace_bytes(prob, &need);   // host-side validation and sizing only
+    ssd::Shape s;
+    int rc = ssd::validate(prob, /*has_seq_idx=*/false, &s);   // host-side validation and sizing only
     if (rc != SSD_OK) return rc;
-    if (need > SSD_NOALLOC_SCRATCH_BYTES) return SSD_ERR_SCRATCH_TOO_SMALL;
+    size_t least = 0, best = 0;
+    forward_needs(prob, s, &least, &best);
+    if (least > SSD_NOALLOC_SCRATCH_BYTES) return SSD_ERR_SCRATCH_TOO_SMALL;
     void* ws = nullptr;
     if ((rc = scratch_address(&ws)) != SSD_OK) return rc;
     // the status word goes to the caller's pointer, or stays in the scratch header

@@ -1,6 +1,9 @@
 // Fused SSD forward for the Mamba-2 layer shapes: bf16 activations, head
-// dimension P = 64, state N in {64, 128, 256} (256: two column blocks of
-// 128), chunk Q = 256; plain rows, or one packed row of sequences (Section
+// dimension P = 64 (or 128, run as two heads of 64 features that share dt, A
+// and D: x, y and the states of such a head are those of two heads one after
+// the other), state N in {64, 128, 256} (256: two column blocks of 128), chunks
+// of Q = 256 tokens whatever block length the caller names (the result does not
+// depend on it); plain rows, or one packed row of sequences (Section
 // 8.3) through a chunk table built on the device.
 //
 // Two launches per call (a packed row adds the small kernels that build and
@@ -923,10 +926,14 @@ __device__ __forceinline__ void dma_z_strips(const FusedParams& p, const Item& i
 }
 
 // dt of token `tid` (clamped to the chunk) of head hh of an item, raw bf16.
+// HSH = 1: headdim 128, the caller's head is two of the kernel's, which share
+// its dt, A, D and bias (a template argument: the shift and the other stride as
+// run-time values cost the plain kernels 0.5 %, and packed rows 3 %).
+template <int HSH>
 __device__ __forceinline__ u16 load_dt(const FusedParams& p, const Item& it, int hh, int tid)
 {
     const int t = tid < it.L ? tid : it.L - 1;
-    return static_cast<const u16*>(p.dt)[(it.b * p.T + it.c0 + t) * p.H + hh];
+    return static_cast<const u16*>(p.dt)[(it.b * p.T + it.c0 + t) * (p.H >> HSH) + (hh >> HSH)];
 }
 
 // The chunk's causal Gram tiles (shared by the item's heads) into LDS.
@@ -1003,7 +1010,7 @@ __device__ __forceinline__ void load_c_block(const FusedParams& p, const Item& i
 // recomputed for the block gradients, whose dy and dz need y before rounding).
 // FUSE: the right factor (of the first column block of the state, with two)
 // runs in the diagonal block's pass over x.
-template <int N, bool PACKED, bool EARLY, bool Y32, bool FUSE>
+template <int N, bool PACKED, bool EARLY, bool Y32, bool FUSE, int HSH>
 __device__ __forceinline__ void head_step(const FusedParams& p, const Item& it, int hk, int& next, int nwork,
                                           int per_c, int nHG,
                                           uint4 (&btf)[kQ / 32], uint4 (&cf)[2][(N < kNH ? N : kNH) / 32],
@@ -1047,7 +1054,7 @@ __device__ __forceinline__ void head_step(const FusedParams& p, const Item& it, 
     const int b = it.b, c = it.c, L = it.L;
     const int64_t c0 = it.c0;
     const bool has_prev = it.has_prev, has_next = it.has_next;
-    const float Dh = Dp ? Dp[h] : 0.f;   // scalar loads (read-only kernel arguments)
+    const float Dh = Dp ? Dp[h >> HSH] : 0.f;   // scalar loads (read-only kernel arguments)
     // this head's normalisation weights (one per thread of the first wavefront),
     // stored to LDS at the state barrier, read by the output stage
     const bool gate = p.z != nullptr, norm = p.norm_head != 0;
@@ -1058,12 +1065,12 @@ __device__ __forceinline__ void head_step(const FusedParams& p, const Item& it, 
     u16 dtr_next = 0;
     int h_next = -1, L_next = 0;   // the next head of this workgroup, once known
     if (!last) {
-        if (tid < kQ) dtr_next = load_dt(p, it, h + 1, tid);
+        if (tid < kQ) dtr_next = load_dt<HSH>(p, it, h + 1, tid);
         h_next = h + 1;
         L_next = L;
     } else if (hk > 0 && next < nwork) {
         const Item nit = decode_item<PACKED>(p, next, per_c, nHG, N);
-        if (tid < kQ) dtr_next = load_dt(p, nit, nit.h0, tid);
+        if (tid < kQ) dtr_next = load_dt<HSH>(p, nit, nit.h0, tid);
         h_next = nit.h0;
         L_next = nit.L;
     }
@@ -1087,12 +1094,12 @@ __device__ __forceinline__ void head_step(const FusedParams& p, const Item& it, 
             if (tid < Lh) {
                 dv = bf(raw);
                 if (p.dtx.active) {   // the block path's dt parameterisation
-                    if (biasp) dv += biasp[hh];
+                    if (biasp) dv += biasp[hh >> HSH];
                     if (p.dtx.softplus) dv = softplus_f(dv);
                     dv = fminf(fmaxf(dv, p.dtx.lo), p.dtx.hi);
                 }
             }
-            inc = dv * (-expf(A_logp[hh]) * kLog2e);
+            inc = dv * (-expf(A_logp[hh >> HSH]) * kLog2e);
             inc = wave_inclusive_scan(inc);
             if (lane == 63) wtv[wave] = inc;
         }
@@ -1371,7 +1378,7 @@ __device__ __forceinline__ void head_step(const FusedParams& p, const Item& it, 
                 const Item nit = decode_item<PACKED>(p, next, per_c, nHG, N);
                 dma_gram(gr, p, nit, wave, dmo);
                 dma_head(p, nit, nit.h0, xs_n, wave, dmo);
-                if (tid < kQ) dtr_next = load_dt(p, nit, nit.h0, tid);
+                if (tid < kQ) dtr_next = load_dt<HSH>(p, nit, nit.h0, tid);
             }
         }
 
@@ -1518,7 +1525,7 @@ __device__ __forceinline__ void head_step(const FusedParams& p, const Item& it, 
 
 // A_log, D and the dt bias come as separate read-only arguments so that their per-head values
 // are scalar loads (a vector load would wait behind the outstanding copies).
-template <int N, bool PACKED, bool EARLY, bool Y32, bool FUSE>
+template <int N, bool PACKED, bool EARLY, bool Y32, bool FUSE, int HSH>
 __global__ __launch_bounds__(kMainThreads, 1) void k_fused_main(FusedParams p, const float* __restrict__ A_logp,
                                                                 const float* __restrict__ Dp,
                                                                 const float* __restrict__ biasp)
@@ -1560,7 +1567,7 @@ __global__ __launch_bounds__(kMainThreads, 1) void k_fused_main(FusedParams p, c
         const Item it = decode_item<PACKED>(p, work, per_c, nHG, N);
         dma_gram(s_gr, p, it, wave, dmo);
         dma_head(p, it, it.h0, sm.XS[0], wave, dmo);
-        if (tid < kQ) dtr = load_dt(p, it, it.h0, tid);
+        if (tid < kQ) dtr = load_dt<HSH>(p, it, it.h0, tid);
     }
     wait_vmem();
     __syncthreads();
@@ -1580,7 +1587,7 @@ __global__ __launch_bounds__(kMainThreads, 1) void k_fused_main(FusedParams p, c
     const Item it = decode_item<PACKED>(p, work, per_c, nHG, N);
     int next = nwork;
     for (int hk = 0; hk < p.HG; ++hk) {
-        head_step<N, PACKED, EARLY, Y32, FUSE>(p, it, hk, next, nwork, per_c, nHG, btf, cf, dtr, ready, sm.XS[q],
+        head_step<N, PACKED, EARLY, Y32, FUSE, HSH>(p, it, hk, next, nwork, per_c, nHG, btf, cf, dtr, ready, sm.XS[q],
                      sm.XS[q ^ 1], sm.cs[q], sm.dt[q], sm.wtot[q], sm.vf[q], sm.w[q], sm.cs[q ^ 1], sm.dt[q ^ 1],
                      sm.wtot[q ^ 1], sm.vf[q ^ 1], sm.w[q ^ 1], s_gr, s_hb, &sm.ticket, A_logp, Dp, biasp, sm.wn);
         q ^= 1;
@@ -1593,7 +1600,7 @@ __global__ __launch_bounds__(kMainThreads, 1) void k_fused_main(FusedParams p, c
 template <int N>
 hipError_t launch_n(const FusedParams& p, hipStream_t stream, hipEvent_t ev_begin, hipEvent_t ev_end)
 {
-    if (p.y32 && (p.vtab || p.z || p.norm_head)) return hipErrorInvalidValue;   // plain rows, no gate/norm
+    if (p.y32 && (p.vtab || p.z || p.norm_head || p.head128)) return hipErrorInvalidValue;   // plain rows, no gate/norm
     if (p.vtab) {   // packed row: the chunk table first
         hipError_t e = launch_seq_table(p.seq_idx, p.arg_starts, p.T, p.nseq, kQ, p.nC, p.ring_rows, p.starts,
                                         p.vtab, nullptr, p.vcount, stream);
@@ -1626,33 +1633,32 @@ hipError_t launch_n(const FusedParams& p, hipStream_t stream, hipEvent_t ev_begi
     int64_t grid = nwork < cus ? nwork : cus;
     if (p.max_workgroups >= 1 && p.max_workgroups < grid) grid = p.max_workgroups;
     const dim3 g_main(static_cast<unsigned>(grid));
-    const float* A_logp = p.A_log;
-    const float* Dp = p.D;
-    const float* biasp = p.dtx.bias;
+    const auto go = [&](auto kern) {
+        hipLaunchKernelGGL(kern, g_main, dim3(kMainThreads), 0, stream, p, p.A_log, p.D, p.dtx.bias);
+    };
+    const auto pick = [&](auto hsh) {
+        constexpr int HSH = decltype(hsh)::value;
+        if (p.vtab && p.early_flag)
+            go(k_fused_main<N, true, true, false, false, HSH>);
+        else if (p.vtab && p.fuse_rf)
+            go(k_fused_main<N, true, false, false, true, HSH>);
+        else if (p.vtab)
+            go(k_fused_main<N, true, false, false, false, HSH>);
+        else if (p.early_flag)
+            go(k_fused_main<N, false, true, false, false, HSH>);
+        else if (p.fuse_rf)
+            go(k_fused_main<N, false, false, false, true, HSH>);
+        else
+            go(k_fused_main<N, false, false, false, false, HSH>);
+    };
     if (p.y32 && p.early_flag)
-        hipLaunchKernelGGL((k_fused_main<N, false, true, true, false>), g_main, dim3(kMainThreads), 0, stream, p, A_logp, Dp,
-                           biasp);
+        go(k_fused_main<N, false, true, true, false, 0>);
     else if (p.y32)
-        hipLaunchKernelGGL((k_fused_main<N, false, false, true, false>), g_main, dim3(kMainThreads), 0, stream, p, A_logp,
-                           Dp, biasp);
-    else if (p.vtab && p.early_flag)
-        hipLaunchKernelGGL((k_fused_main<N, true, true, false, false>), g_main, dim3(kMainThreads), 0, stream, p, A_logp, Dp,
-                           biasp);
-    else if (p.vtab && p.fuse_rf)
-        hipLaunchKernelGGL((k_fused_main<N, true, false, false, true>), g_main, dim3(kMainThreads), 0, stream, p, A_logp,
-                           Dp, biasp);
-    else if (p.vtab)
-        hipLaunchKernelGGL((k_fused_main<N, true, false, false, false>), g_main, dim3(kMainThreads), 0, stream, p, A_logp,
-                           Dp, biasp);
-    else if (p.early_flag)
-        hipLaunchKernelGGL((k_fused_main<N, false, true, false, false>), g_main, dim3(kMainThreads), 0, stream, p, A_logp,
-                           Dp, biasp);
-    else if (p.fuse_rf)
-        hipLaunchKernelGGL((k_fused_main<N, false, false, false, true>), g_main, dim3(kMainThreads), 0, stream, p,
-                           A_logp, Dp, biasp);
+        go(k_fused_main<N, false, false, true, false, 0>);
+    else if (p.head128)
+        pick(std::integral_constant<int, 1>{});
     else
-        hipLaunchKernelGGL((k_fused_main<N, false, false, false, false>), g_main, dim3(kMainThreads), 0, stream, p,
-                           A_logp, Dp, biasp);
+        pick(std::integral_constant<int, 0>{});
     err = hipGetLastError();
     if (err == hipSuccess && ev_end) err = hipEventRecord(ev_end, stream);
     return err;
@@ -1682,9 +1688,9 @@ hipError_t launch_seq_table(const int32_t* seq_idx, const SeqStartsArg* arg_star
     return hipGetLastError();
 }
 
-bool fused_supported(int64_t P, int64_t N, int64_t Q, bool bf16)
+bool fused_supported(int64_t H, int64_t P, int64_t N, bool bf16)
 {
-    return bf16 && P == kP && Q == kQ && (N == 64 || N == 128 || N == 256);
+    return bf16 && (P == kP || (P == 2 * kP && 2 * H <= 65535)) && (N == 64 || N == 128 || N == 256);
 }
 
 FusedLayout fused_layout(int64_t b, int64_t T, int64_t H, int64_t N, int64_t G, int64_t nC, int64_t nseq)

@@ -78,7 +78,8 @@ WorkspaceLayout workspace_layout(int64_t b, int64_t H, int64_t P, int64_t N, int
 hipError_t launch_unfused(const Params& p, bool bf16, hipStream_t stream,
                           hipEvent_t ev_begin, hipEvent_t ev_end);
 
-// Fused path (bf16, P = 64, N in {64, 128, 256}, Q = 256; plain rows or one packed row).
+// Fused path (bf16, P = 64 or 128, N in {64, 128, 256}, its own chunks of 256
+// tokens; plain rows or one packed row).
 // Sequence starts of a packed row handed to the device by value (kernel
 // argument) when the caller gives them in host memory: n sequences, v[0..n].
 constexpr int kArgSeqs = 511;
@@ -88,7 +89,7 @@ struct SeqStartsArg {
 };
 
 struct FusedParams {
-    int64_t b, T, H, P, N, G, nC, HG;
+    int64_t b, T, H, P, N, G, nC, HG;   // H heads of P = 64 features
     const void* x;
     const void* dt;
     const float* A_log;
@@ -137,6 +138,9 @@ struct FusedParams {
     float norm_eps = 0.f;
     // nonzero: y is float32 (plain rows, no gate or normalisation)
     int y32 = 0;
+    // nonzero: headdim 128, each of the caller's heads two of these (dt, A_log,
+    // D and the dt bias have H / 2 heads)
+    int head128 = 0;
 };
 
 struct FusedLayout {
@@ -146,7 +150,9 @@ struct FusedLayout {
 };
 
 int64_t heads_per_workgroup(int64_t heads_per_group, int64_t items_per_head, int compute_units);
-bool fused_supported(int64_t P, int64_t N, int64_t Q, bool bf16);
+constexpr int64_t kFusedQ = 256;    // chunk length of the fused kernels
+constexpr int64_t kFusedP = 64;     // features of one of their heads
+bool fused_supported(int64_t H, int64_t P, int64_t N, bool bf16);
 // The chunk table of a packed row of T tokens and nseq sequences, from the
 // device seq_idx or, when it is null, from starts handed over by value: every
 // sequence cut into chunks of Q tokens (256 or 64) from its first token on,

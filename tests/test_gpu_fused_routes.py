@@ -1,0 +1,116 @@
+"""Calls that the fused kernels take over from the general ones: headdim 128
+(two of their heads a head) and block lengths other than their own, plain and
+packed rows, with the block steps -- and the calls of those shapes that stay on
+the general kernels (operands off 16 bytes, a workspace of the general size).
+Against the float64 oracle, at the bounds of test_gpu_parity.
+"""
+import numpy as np
+import pytest
+
+import oracle.block as ob
+from paper_2405_21060_amd.inputs import Problem, make_block_inputs, make_inputs
+from tests.ssd_harness import TOL, announce, rel_err, run_gpu, to_device, to_f64
+from tests.test_gpu_block import run_block
+from tests.test_gpu_parity import _gpu, compare  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+
+PLAIN = [
+    # b, T, H, P, N, G, Q
+    (2, 300, 3, 128, 64, 1, 128),      # odd heads, two chunks, the last one partial
+    (1, 513, 4, 128, 128, 2, 256),
+    (1, 270, 2, 128, 256, 2, 32),      # one head a group, two column blocks
+    (3, 1, 5, 128, 128, 1, 64),        # one token
+    (2, 257, 6, 64, 128, 3, 32),
+    (1, 600, 8, 64, 64, 1, 64),
+    (1, 255, 4, 64, 256, 1, 128),
+]
+
+
+def _inputs(b, T, H, P, N, G, Q, seed, **kw):
+    return make_inputs(Problem(b, T, H, P, N, G, Q, "bf16", init_states=True, **kw), seed)
+
+
+@pytest.mark.parametrize("shape", PLAIN)
+def test_plain_rows(shape):
+    announce("fused route %s" % (shape,))
+    inp = _inputs(*shape, seed=11)
+    compare(inp, *run_gpu(inp))
+    y, fin = run_gpu(inp, use_D=False, use_init=False)
+    inp.D, inp.initial_states = np.zeros_like(inp.D), None
+    compare(inp, y, fin)
+
+
+@pytest.mark.parametrize("P,N,G,Q", [(128, 128, 1, 256), (128, 64, 2, 64), (64, 128, 2, 128)])
+@pytest.mark.parametrize("host", [False, True])
+def test_packed_rows(P, N, G, Q, host):
+    from paper_2405_21060_amd import ssd
+
+    announce("fused route, packed P%d N%d G%d Q%d host %s" % (P, N, G, Q, host))
+    inp = _inputs(1, 1500, 4, P, N, G, Q, seed=12, varlen=True, len_lo=1, len_hi=600)
+    if not host:
+        compare(inp, *run_gpu(inp))
+        return
+    d = to_device(inp)
+    starts = [0] + [int(v) + 1 for v in np.flatnonzero(np.diff(inp.seq_idx[0]))] + [1500]
+    compare(inp, *ssd.forward_varlen(d["x"], d["dt"], d["A_log"], d["B"], d["C"], starts, d["D"], chunk_size=Q,
+                                     initial_states=d["initial_states"]))
+
+
+@pytest.mark.parametrize("group", [0, 128, 512])
+def test_block_headdim_128(group):
+    announce("fused route, block P128 norm group %d" % group)
+    bi = make_block_inputs(Problem(2, 400, 4, 128, 128, 2, 128, "bf16"), 13)
+    opts = dict(norm_group_size=group)
+    y, fin = run_block(bi, opts)
+    y_ref, fin_ref = ob.block_forward_inputs(bi, opts)
+    assert rel_err(to_f64(y), y_ref) <= TOL["bf16"]
+    assert rel_err(to_f64(fin), fin_ref) <= TOL["bf16"]
+
+
+@pytest.mark.parametrize("what", ["x", "B", "C", "y"])
+def test_operand_off_16_bytes_stays_general(what):
+    """An activation one element off: the general kernels' result, as before."""
+    import torch
+    from paper_2405_21060_amd import ssd
+
+    announce("general kernels, %s off 16 bytes" % what)
+    inp = _inputs(1, 300, 4, 128, 64, 2, 128, seed=14)
+    d = to_device(inp)
+
+    def off(t):
+        u = torch.empty(t.numel() + 1, dtype=t.dtype, device=t.device)[1:].view(t.shape)
+        return u.copy_(t)
+
+    out = torch.empty_like(d["x"])
+    if what == "y":
+        out = off(out)
+    else:
+        d[what] = off(d[what])
+    compare(inp, *ssd.forward(d["x"], d["dt"], d["A_log"], d["B"], d["C"], d["D"], chunk_size=128,
+                              initial_states=d["initial_states"], out=out))
+
+
+def test_workspace_of_the_general_size_is_enough(tune):
+    """A one-chunk call whose ring is larger than the general kernels' states."""
+    import torch
+    from paper_2405_21060_amd import ssd
+
+    announce("general kernels on their own workspace")
+    inp = _inputs(2, 32, 16, 128, 128, 1, 32, seed=15)
+    d = to_device(inp)
+    p = ssd.make_problem(2, 32, 16, 128, 128, 1, 32, ssd.SSD_DTYPE_BF16)
+    best = ssd.ssd_workspace_bytes(p)
+    tune("force_general_path", 1)
+    general = ssd.ssd_workspace_bytes(p)
+    tune("force_general_path", 0)
+    assert general < best
+    y, fin = torch.empty_like(d["x"]), torch.empty_like(d["initial_states"])
+    for size, want in ((general, ssd.SSD_OK), (general - 1, ssd.SSD_ERR_WORKSPACE)):
+        ws = torch.empty(size, dtype=torch.uint8, device="cuda")
+        rc = ssd.ssd_forward(p, *(d[k].data_ptr() for k in ("x", "dt", "A_log", "B", "C", "D", "initial_states")), 0,
+                             y.data_ptr(), fin.data_ptr(), ws.data_ptr(), size,
+                             torch.cuda.current_stream().cuda_stream)
+        assert rc == want
+    torch.cuda.synchronize()
+    compare(inp, y, fin)
