@@ -1,16 +1,13 @@
 // Device-side building blocks shared by the SSD kernels (gfx950 / CDNA4).
 //
 // Matrix-core convention used throughout.  A 16x16 output tile is produced by
-// "K-steps" of 32 contraction indices.  In a K-step every lane l holds eight
-// values of each operand: lane row/column r = l & 15, lane group g = l >> 4,
-// slot e = 0..7 carries contraction index k = kmap(g, e).  The A operand's
-// lane holds row r (A[r][k]), the B operand's lane holds column r (B[k][r]).
-// Any kmap that is a bijection onto the 32 indices gives the same sum, because
-// both operands use the same lane/slot -> k assignment.
-//   * bf16: one v_mfma_f32_16x16x32_bf16 (slot e of group g is one of its k);
-//   * f32 : eight v_mfma_f32_16x16x4_f32, instruction e contracting the four
-//           values {slot e of group 0..3}.
-// The accumulator (4 floats per lane) holds D[4 g + v][r], v = 0..3.
+// contraction steps in which lane l holds row (A operand) or column (B operand)
+// r = l & 15 and, by its lane group g = l >> 4, some of the contraction indices:
+//   * bf16: v_mfma_f32_16x16x32_bf16, eight indices per lane (32 a step);
+//   * f32 : v_mfma_f32_16x16x4_f32, one index per lane (4 a step).
+// Any assignment of indices to (group, slot) gives the same sum, as long as
+// both operands use the same one.  The accumulator (4 floats per lane) holds
+// D[4 g + v][r], v = 0..3.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -22,10 +19,6 @@ typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
 
 constexpr float kLog2e = 1.4426950408889634f;
-
-struct Frag8 {
-    float v[8];
-};
 
 // Activation element access: float, or bfloat16 stored as its 16 bits.
 template <typename T>
@@ -55,25 +48,6 @@ struct Act<uint16_t> {
         p[i] = static_cast<uint16_t>(u >> 16);
     }
 };
-
-__device__ __forceinline__ f32x4_t mma_step(const Frag8& a, const Frag8& b, f32x4_t c, uint16_t)
-{
-    bf16x8_t av, bv;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-        av[e] = static_cast<__bf16>(a.v[e]);
-        bv[e] = static_cast<__bf16>(b.v[e]);
-    }
-    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, bv, c, 0, 0, 0);
-}
-
-__device__ __forceinline__ f32x4_t mma_step(const Frag8& a, const Frag8& b, f32x4_t c, float)
-{
-#pragma unroll
-    for (int e = 0; e < 8; ++e)
-        c = __builtin_amdgcn_mfma_f32_16x16x4f32(a.v[e], b.v[e], c, 0, 0, 0);
-    return c;
-}
 
 __device__ __forceinline__ f32x4_t zero4()
 {

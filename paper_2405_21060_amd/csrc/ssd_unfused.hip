@@ -27,8 +27,55 @@ namespace {
 
 constexpr int kThreads = 256;  // 4 wavefronts
 constexpr int kMaxQ = 256;
-constexpr int kSlab = 32;      // tokens per staged K-step
-constexpr int kPad = kSlab + 1;
+constexpr int kSlab = 64;      // tokens of x (and B) staged in LDS at a time
+constexpr int kNB = 64;        // state columns staged in LDS at a time
+
+// Four consecutive activations as floats.  Rows are multiples of 16 elements,
+// but the caller's pointers need only be aligned to their own type, so the
+// vectors say so (the hardware reads and writes them at any alignment).
+typedef float f4u_t __attribute__((ext_vector_type(4), aligned(4)));
+typedef uint16_t h4u_t __attribute__((ext_vector_type(4), aligned(2)));
+
+__device__ __forceinline__ f32x4_t load4(const float* p)
+{
+    const f4u_t v = *reinterpret_cast<const f4u_t*>(p);
+    return f32x4_t{v.x, v.y, v.z, v.w};
+}
+
+__device__ __forceinline__ f32x4_t load4(const uint16_t* p)
+{
+    const h4u_t v = *reinterpret_cast<const h4u_t*>(p);
+    f32x4_t f;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) f[e] = __uint_as_float(static_cast<uint32_t>(v[e]) << 16);
+    return f;
+}
+
+__device__ __forceinline__ void store4(float* p, f32x4_t v) { *reinterpret_cast<f4u_t*>(p) = f4u_t{v[0], v[1], v[2], v[3]}; }
+
+__device__ __forceinline__ void store4(uint16_t* p, f32x4_t v)
+{
+    h4u_t h;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        uint16_t u;
+        Act<uint16_t>::store(&u, 0, v[e]);   // round to nearest even
+        h[e] = u;
+    }
+    *reinterpret_cast<h4u_t*>(p) = h;
+}
+
+// One float32 matrix instruction: D[4 g + v][r] += sum over the lane groups
+// g' = 0..3 of A (row r of the lane) x B (column r of the lane).
+__device__ __forceinline__ f32x4_t mma4(float a, float b, f32x4_t c)
+{
+    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+}
+
+// Sixteen wait states between matrix instructions of a loop with a run-time
+// trip count and the first read of their results after it (the compiler has
+// been seen to leave too few on one path out of such a loop).
+__device__ __forceinline__ void settle(f32x4_t& a) { asm volatile("s_nop 15" : "+v"(a)); }
 
 // Sequence ids outside [0, nseq) break the seq_idx contract; state reads and
 // writes for them are skipped so that such input cannot fault the device.
@@ -102,104 +149,147 @@ __global__ __launch_bounds__(kThreads) void k_chunk_prep(Params p)
     }
 }
 
-// G[t][s] = sum_n C_t[n] B_s[n] for 16x16 tiles with s-tile <= t-tile.
+// G[t][s] = sum_n C_t[n] B_s[n] for 16x16 tiles with s-tile <= t-tile; one
+// workgroup per 16-token strip of t, its s-tiles dealt to the wavefronts.  The
+// operands come straight from global memory as 16-byte pieces of rows: lane
+// group g takes columns 16 k + 4 g .. + 3, one per matrix instruction (the same
+// permutation of the contraction on both sides).  Bound by those loads'
+// latency (the whole Gram is a few per cent of the forward's products), hence
+// a workgroup per strip: at 2 x 2048 tokens, N 128, float32 13 us, where one
+// workgroup per chunk with 4-byte loads took 236.
 template <typename T>
-__global__ __launch_bounds__(kThreads) void k_gram(Params p)
+__global__ __launch_bounds__(kThreads) void k_gram(Params p, int split)
 {
-    const int c = blockIdx.x, g = blockIdx.y, b = blockIdx.z;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, r = lane & 15, lg = lane >> 4;
-    const int64_t c0 = static_cast<int64_t>(c) * p.Q;
-    const int L = chunk_len(p, c);
     const int nq = static_cast<int>(p.Q / 16);
-    const int ntile = nq * (nq + 1) / 2;
-    const T* Bp = static_cast<const T*>(p.B);
-    const T* Cp = static_cast<const T*>(p.C);
+    const int c = blockIdx.x / split, g = blockIdx.y, b = blockIdx.z;
+    const int lane = threadIdx.x & 63, r = lane & 15, lg = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t c0 = static_cast<int64_t>(c) * p.Q;
+    const int L = chunk_len(p, c), N = static_cast<int>(p.N);
+    const int64_t row = p.G * p.N;
+    const T* Bp = static_cast<const T*>(p.B) + ((b * p.T + c0) * p.G + g) * p.N + 4 * lg;
+    const T* Cp = static_cast<const T*>(p.C) + ((b * p.T + c0) * p.G + g) * p.N + 4 * lg;
     float* Gp = p.gram + ((b * p.G + g) * p.nC + c) * p.Q * p.Q;
-    for (int tau = wave; tau < ntile; tau += kThreads / 64) {
-        int i = 0;
-        while ((i + 1) * (i + 2) / 2 <= tau) ++i;
-        const int j = tau - i * (i + 1) / 2;
-        const int t = 16 * i + r, s = 16 * j + r;
-        f32x4_t acc = zero4();
-        for (int k0 = 0; k0 < p.N; k0 += 32) {
-            Frag8 fa, fb;
+    // (strips past a partial chunk: tiles that no token reads)
+    for (int i = blockIdx.x % split; i < nq && 16 * i < L; i += split) {
+        const int t = 16 * i + r;
+        const T* crow = Cp + (t < L ? t : L - 1) * row;
+        for (int j = wave; j <= i; j += kThreads / 64) {
+            const int s = 16 * j + r;
+            const T* brow = Bp + (s < L ? s : L - 1) * row;
+            f32x4_t acc = zero4();
+#pragma unroll 4
+            for (int k = 0; k < N; k += 16) {
+                const f32x4_t cv = load4(crow + k), bv = load4(brow + k);
 #pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const int n = k0 + 8 * lg + e;
-                fa.v[e] = (t < L && n < p.N) ? Act<T>::load(Cp, ((b * p.T + c0 + t) * p.G + g) * p.N + n) : 0.f;
-                fb.v[e] = (s < L && n < p.N) ? Act<T>::load(Bp, ((b * p.T + c0 + s) * p.G + g) * p.N + n) : 0.f;
+                for (int v = 0; v < 4; ++v) acc = mma4(bv[v], cv[v], acc);
             }
-            acc = mma_step(fa, fb, acc, T());
-        }
+            settle(acc);
+            // lane: row t, columns 16 j + 4 lg .. + 3 (rows past a partial chunk: zeros)
 #pragma unroll
-        for (int v = 0; v < 4; ++v) Gp[(16 * i + 4 * lg + v) * p.Q + 16 * j + r] = acc[v];
+            for (int v = 0; v < 4; ++v)
+                if (t >= L || 16 * j + 4 * lg + v >= L) acc[v] = 0.f;
+            store4(Gp + t * p.Q + 16 * j + 4 * lg, acc);
+        }
     }
 }
 
-// Sum over the tokens s of [st, en] of w_s x_s B_s^T into a (P x N) tile set,
-// w_s = dt_s exp2(cs2_en - cs2_s); the result (plus hin_scale * hin, when hin
-// is given) is stored to dst (P x N, row-major).  Block-uniform call.
-template <typename T>
-__device__ void segment_state(const Params& p, int b, int c, int h, int g, int st, int en,
-                              const float* cs_s, const float* dt_s, float* w_s, float* xT,
-                              float* BT, float* dst, const float* hin, float hin_scale)
-{
-    constexpr int kMaxTiles = 32;  // (128/16) * (256/16) / 4 waves
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, r = lane & 15, lg = lane >> 4;
-    const int P = static_cast<int>(p.P), N = static_cast<int>(p.N);
-    const int TN = N / 16, ntiles = (P / 16) * TN;
-    const int64_t c0 = static_cast<int64_t>(c) * p.Q;
-    const T* xp = static_cast<const T*>(p.x);
-    const T* Bp = static_cast<const T*>(p.B);
+// Right factors run on 64 x 64 tiles (features x columns) of the P x N state,
+// one workgroup each, a 2 x 2 block of 16 x 16 tiles per wavefront.  The
+// tokens arrive in slabs of 64, x scaled by its weight, both token-major in
+// LDS with a row stride of 80 floats (the four rows that one matrix
+// instruction's operand reads fall in different banks).  Bound by the float32
+// matrix rate: at 2 x 2048 tokens, 24 heads, P 64, N 128 26 us for 1.6 GFLOP;
+// the 4-byte loads and one workgroup per whole state that it replaces took 142.
+constexpr int kTile = 64;
+constexpr int kTS = kTile + 16;
 
-    for (int t = threadIdx.x; t < kMaxQ; t += kThreads)
+struct StateSmem {
+    float X[kSlab * kTS], B[kSlab * kTS];
+};
+
+__host__ __device__ __forceinline__ int state_tiles(int64_t P, int64_t N)
+{
+    return static_cast<int>(((P + kTile - 1) / kTile) * ((N + kTile - 1) / kTile));
+}
+
+// Sum over the tokens s of [st, en] of w_s x_s B_s^T over tile `tile` of the
+// (P x N) state, w_s = dt_s exp2(cs2_en - cs2_s); the result (plus hin_scale *
+// hin, when hin is given) is stored to dst (P x N, row-major).  Block-uniform call.
+template <typename T>
+__device__ void segment_state(const Params& p, int b, int c, int h, int g, int tile, int st, int en,
+                              const float* cs_s, const float* dt_s, float* w_s, StateSmem& sm, float* dst,
+                              const float* hin, float hin_scale)
+{
+    const int tid = threadIdx.x, lane = tid & 63, r = lane & 15, lg = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int P = static_cast<int>(p.P), N = static_cast<int>(p.N);
+    const int ntn = (N + kTile - 1) / kTile;
+    const int p0 = (tile / ntn) * kTile, n0 = (tile % ntn) * kTile;
+    const int64_t c0 = static_cast<int64_t>(c) * p.Q;
+    const T* xp = static_cast<const T*>(p.x) + ((b * p.T + c0) * p.H + h) * p.P + p0;
+    const T* Bp = static_cast<const T*>(p.B) + ((b * p.T + c0) * p.G + g) * p.N + n0;
+    const int64_t xrow = p.H * p.P, brow = p.G * p.N;
+    const int pw = 32 * (wave & 1), nw = 32 * (wave >> 1);   // this wavefront's 32 x 32 of the tile
+
+    for (int t = tid; t < kMaxQ; t += kThreads)
         w_s[t] = (t >= st && t <= en) ? dt_s[t] * exp2f(cs_s[en] - cs_s[t]) : 0.f;
     __syncthreads();
 
-    f32x4_t acc[kMaxTiles];
+    f32x4_t acc[2][2];   // [p-tile][n-tile]: lane holds S[p = r][n = 4 lg + v]
 #pragma unroll
-    for (int k = 0; k < kMaxTiles; ++k) acc[k] = zero4();
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) acc[i][j] = zero4();
 
     for (int s0 = (st / kSlab) * kSlab; s0 <= en; s0 += kSlab) {
-        for (int idx = threadIdx.x; idx < kSlab * P; idx += kThreads) {
-            const int ss = idx / P, pp = idx % P, s = s0 + ss;
-            xT[pp * kPad + ss] = (s <= en) ? Act<T>::load(xp, ((b * p.T + c0 + s) * p.H + h) * p.P + pp) * w_s[s] : 0.f;
+        constexpr int kPer = kSlab * kTile / 4 / kThreads;   // 4-wide pieces per thread
+        f32x4_t vx[kPer], vb[kPer];
+#pragma unroll
+        for (int k = 0; k < kPer; ++k) {
+            const int i = tid + kThreads * k, s = s0 + i / (kTile / 4), f = 4 * (i % (kTile / 4));
+            vx[k] = vb[k] = zero4();
+            if (s >= st && s <= en) {
+                if (p0 + f < P) vx[k] = load4(xp + s * xrow + f);
+                if (n0 + f < N) vb[k] = load4(Bp + s * brow + f);
+            }
         }
-        for (int idx = threadIdx.x; idx < kSlab * N; idx += kThreads) {
-            const int ss = idx / N, n = idx % N, s = s0 + ss;
-            BT[n * kPad + ss] = (s <= en) ? Act<T>::load(Bp, ((b * p.T + c0 + s) * p.G + g) * p.N + n) : 0.f;
+#pragma unroll
+        for (int k = 0; k < kPer; ++k) {
+            const int i = tid + kThreads * k, ss = i / (kTile / 4), f = 4 * (i % (kTile / 4));
+            const float ws = w_s[s0 + ss];
+            *reinterpret_cast<f32x4_t*>(&sm.X[ss * kTS + f]) = f32x4_t{vx[k][0] * ws, vx[k][1] * ws, vx[k][2] * ws, vx[k][3] * ws};
+            *reinterpret_cast<f32x4_t*>(&sm.B[ss * kTS + f]) = vb[k];
         }
         __syncthreads();
+#pragma unroll 4
+        for (int k = 0; k < kSlab / 4; ++k) {
+            const float* xr = &sm.X[(4 * k + lg) * kTS + pw + r];
+            const float* br = &sm.B[(4 * k + lg) * kTS + nw + r];
+            const float x0 = xr[0], x1 = xr[16], b0 = br[0], b1 = br[16];
+            acc[0][0] = mma4(b0, x0, acc[0][0]);
+            acc[0][1] = mma4(b1, x0, acc[0][1]);
+            acc[1][0] = mma4(b0, x1, acc[1][0]);
+            acc[1][1] = mma4(b1, x1, acc[1][1]);
+        }
+        __syncthreads();
+    }
 #pragma unroll
-        for (int k = 0; k < kMaxTiles; ++k) {
-            const int tau = wave + 4 * k;
-            if (tau < ntiles) {
-                const int pt = tau / TN, nt = tau % TN;
-                Frag8 fa, fb;
+    for (int i = 0; i < 2; ++i)
 #pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    fa.v[e] = xT[(16 * pt + r) * kPad + 8 * lg + e];
-                    fb.v[e] = BT[(16 * nt + r) * kPad + 8 * lg + e];
+        for (int j = 0; j < 2; ++j) {
+            settle(acc[i][j]);
+            const int pp = p0 + pw + 16 * i + r, n = n0 + nw + 16 * j + 4 * lg;
+            if (pp < P && n < N) {
+                f32x4_t val = acc[i][j];
+                if (hin) {
+                    const f32x4_t hv = load4(hin + pp * N + n);
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) val[v] += hin_scale * hv[v];
                 }
-                acc[k] = mma_step(fa, fb, acc[k], T());
+                store4(dst + pp * N + n, val);
             }
         }
-        __syncthreads();
-    }
-#pragma unroll
-    for (int k = 0; k < kMaxTiles; ++k) {
-        const int tau = wave + 4 * k;
-        if (tau < ntiles) {
-            const int pt = tau / TN, nt = tau % TN;
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const int pp = 16 * pt + 4 * lg + v, n = 16 * nt + r;
-                float val = acc[k][v];
-                if (hin) val += hin_scale * hin[pp * N + n];
-                dst[pp * N + n] = val;
-            }
-        }
-    }
     __syncthreads();
 }
 
@@ -224,38 +314,39 @@ __device__ __forceinline__ void load_chunk_scalars(const Params& p, int b, int c
 }
 
 // Right factors: the chunk's state at its last token from a zero start,
-// restricted to the chunk's last segment.
+// restricted to the chunk's last segment.  blockIdx.x: chunk and state tile.
 template <typename T>
-__global__ __launch_bounds__(kThreads) void k_chunk_state(Params p)
+__global__ __launch_bounds__(kThreads) void k_chunk_state(Params p, int split)
 {
-    const int c = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
+    const int tiles = state_tiles(p.P, p.N);
+    const int c = blockIdx.x / split, h = blockIdx.y, b = blockIdx.z;
     const int g = static_cast<int>(h / (p.H / p.G));
     const int L = chunk_len(p, c);
     __shared__ ChunkScalars sh;
-    __shared__ float xT[128 * kPad];
-    __shared__ float BT[256 * kPad];
+    __shared__ __attribute__((aligned(16))) StateSmem sm;
     load_chunk_scalars<T>(p, b, c, h, L, sh);
     int st = 0;
     if (p.seq_idx)
         for (int k = L - 1; k > 0; --k)
             if (sh.q[k - 1] != sh.q[k]) { st = k; break; }
     float* dst = p.states + ((b * p.nC + c) * p.H + h) * p.P * p.N;
-    segment_state<T>(p, b, c, h, g, st, L - 1, sh.cs, sh.dt, sh.w, xT, BT, dst, nullptr, 0.f);
+    for (int tile = blockIdx.x % split; tile < tiles; tile += split)
+        segment_state<T>(p, b, c, h, g, tile, st, L - 1, sh.cs, sh.dt, sh.w, sm, dst, nullptr, 0.f);
 }
 
 // Packed rows: final states of sequences that end before their chunk's last
 // token (those ending on a chunk's last token come out of the scan).
 template <typename T>
-__global__ __launch_bounds__(kThreads) void k_varlen_final(Params p)
+__global__ __launch_bounds__(kThreads) void k_varlen_final(Params p, int split)
 {
-    const int c = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
+    const int tiles = state_tiles(p.P, p.N);
+    const int c = blockIdx.x / split, h = blockIdx.y, b = blockIdx.z;
     const int g = static_cast<int>(h / (p.H / p.G));
     const int64_t c0 = static_cast<int64_t>(c) * p.Q;
     const int L = chunk_len(p, c);
     const int64_t PN = p.P * p.N;
     __shared__ ChunkScalars sh;
-    __shared__ float xT[128 * kPad];
-    __shared__ float BT[256 * kPad];
+    __shared__ __attribute__((aligned(16))) StateSmem sm;
     load_chunk_scalars<T>(p, b, c, h, L, sh);
     int st = 0;
     for (int en = 0; en < L - 1; ++en) {
@@ -266,9 +357,10 @@ __global__ __launch_bounds__(kThreads) void k_varlen_final(Params p)
                                 : (p.init && unit_ok(p, q) ? p.init + (static_cast<int64_t>(q) * p.H + h) * PN : nullptr);
         const float base = (st > 0) ? sh.cs[st - 1] : 0.f;
         if (!unit_ok(p, q)) { st = en + 1; continue; }
-        segment_state<T>(p, b, c, h, g, st, en, sh.cs, sh.dt, sh.w, xT, BT,
-                         p.fin + (static_cast<int64_t>(q) * p.H + h) * PN, hin,
-                         exp2f(sh.cs[en] - base));
+        for (int tile = blockIdx.x % split; tile < tiles; tile += split)
+            segment_state<T>(p, b, c, h, g, tile, st, en, sh.cs, sh.dt, sh.w, sm,
+                             p.fin + (static_cast<int64_t>(q) * p.H + h) * PN, hin,
+                             exp2f(sh.cs[en] - base));
         st = en + 1;
     }
 }
@@ -287,147 +379,200 @@ __global__ __launch_bounds__(kThreads) void k_state_scan(Params p)
         const int64_t u0 = p.seq_idx ? p.seq_idx[0] : b;
         if (unit_ok(p, u0)) hs = p.init[(u0 * p.H + h) * PN + idx];
     }
-    for (int64_t c = 0; c < p.nC; ++c) {
-        const int4 inf = p.info[(b * p.H + h) * p.nC + c];
-        float* slot = p.states + ((b * p.nC + c) * p.H + h) * PN + idx;
-        const float S = *slot;
-        *slot = hs;
-        const float coef = __int_as_float(inf.x);
-        const bool uok = unit_ok(p, inf.y);
-        if (inf.z)
-            hs = (p.init && uok ? coef * p.init[(static_cast<int64_t>(inf.y) * p.H + h) * PN + idx] : 0.f) + S;
-        else
-            hs = coef * hs + S;
-        if (inf.w && p.fin && uok) p.fin[(static_cast<int64_t>(inf.y) * p.H + h) * PN + idx] = hs;
+    // the chunk terms of kAhead chunks are requested together: the walk is a
+    // chain of one multiply-add a chunk, bound by the loads' latency otherwise
+    constexpr int kAhead = 8;
+    for (int64_t cb = 0; cb < p.nC; cb += kAhead) {
+        float S[kAhead];
+        int4 inf[kAhead];
+#pragma unroll
+        for (int k = 0; k < kAhead; ++k) {
+            const int64_t c = cb + k < p.nC ? cb + k : p.nC - 1;
+            S[k] = p.states[((b * p.nC + c) * p.H + h) * PN + idx];
+            inf[k] = p.info[(b * p.H + h) * p.nC + c];
+        }
+#pragma unroll
+        for (int k = 0; k < kAhead; ++k) {
+            if (cb + k >= p.nC) break;
+            p.states[((b * p.nC + cb + k) * p.H + h) * PN + idx] = hs;
+            const float coef = __int_as_float(inf[k].x);
+            const bool uok = unit_ok(p, inf[k].y);
+            if (inf[k].z)
+                hs = (p.init && uok ? coef * p.init[(static_cast<int64_t>(inf[k].y) * p.H + h) * PN + idx] : 0.f) + S[k];
+            else
+                hs = coef * hs + S[k];
+            if (inf[k].w && p.fin && uok) p.fin[(static_cast<int64_t>(inf[k].y) * p.H + h) * PN + idx] = hs;
+        }
     }
 }
 
-template <typename T>
-__global__ __launch_bounds__(kThreads) void k_chunk_output(Params p)
+// Diagonal block, left factor, skip term and store of four 16-token strips of
+// a chunk, one per wavefront, for one head.  The strips of a workgroup are
+// {z, 2m-1-z, 2m+z, 4m-1-z} of the chunk's 4m (equal causal work for every z),
+// dealt to the wavefronts in an order that turns with the head, so that the
+// longest strips do not all fall on one SIMD.  Everything is computed
+// transposed, Y^T[p][t] (lane: token 16 i + r, features 16 pt + 4 lg .. + 3),
+// so that a Gram row piece of four consecutive s, as loaded, is the operand of
+// four matrix instructions after its mask (contraction slot of lane group lg in
+// instruction v: s = 4 lg + v), with x^T read from the slab of 64 tokens in LDS
+// (row stride P + 4 floats: the four rows of an operand in different banks).
+// The entering state is staged in column blocks of 64.  Bound by the float32
+// matrix rate: at 2 x 2048 tokens, 24 heads, P 64, N 128, Q 256 75 us for 3.3
+// GFLOP, where one workgroup per chunk with 4-byte loads took 418.
+template <typename T, int PT>
+__global__ __launch_bounds__(kThreads) void k_chunk_output(Params p, int split)
 {
-    constexpr int kMaxStrips = kMaxQ / 16 / 4;  // strips of 16 rows per wave
-    constexpr int kMaxPT = 128 / 16;
-    const int c = blockIdx.x, h = blockIdx.y, b = blockIdx.z, t0 = threadIdx.x;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, r = lane & 15, lg = lane >> 4;
+    constexpr int P = 16 * PT, XS = P + 4, HS = kNB + 4;
+    const int nq = static_cast<int>(p.Q / 16), nz = nq >= 4 ? nq / 4 : 1;
+    const int c = blockIdx.x / split, h = blockIdx.y, b = blockIdx.z, tid = threadIdx.x;
+    const int lane = tid & 63, r = lane & 15, lg = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int g = static_cast<int>(h / (p.H / p.G));
     const int64_t c0 = static_cast<int64_t>(c) * p.Q;
-    const int L = chunk_len(p, c);
-    const int P = static_cast<int>(p.P), N = static_cast<int>(p.N);
-    const int TP = P / 16, nq = static_cast<int>(p.Q / 16);
-    const int64_t PN = p.P * p.N;
-    const T* xp = static_cast<const T*>(p.x);
-    const T* Cp = static_cast<const T*>(p.C);
+    const int L = chunk_len(p, c), N = static_cast<int>(p.N);
+    const int64_t PN = p.P * p.N, xrow = p.H * P, crow = p.G * p.N;
+    const T* xp = static_cast<const T*>(p.x) + ((b * p.T + c0) * p.H + h) * P;
+    const T* Cp = static_cast<const T*>(p.C) + ((b * p.T + c0) * p.G + g) * p.N;
     const float* Gp = p.gram + ((b * p.G + g) * p.nC + c) * p.Q * p.Q;
-    __shared__ float cs_s[kMaxQ], dt_s[kMaxQ];
-    __shared__ int q_s[kMaxQ];
-    __shared__ float xT[128 * kPad];
+    __shared__ __attribute__((aligned(16))) float cs_s[kMaxQ], dt_s[kMaxQ];
+    __shared__ __attribute__((aligned(16))) int q_s[kMaxQ];
+    __shared__ __attribute__((aligned(16))) float xs[kSlab * XS];
+    __shared__ __attribute__((aligned(16))) float hs[P * HS];
 
-    if (t0 < kMaxQ) {
-        const bool in = t0 < L;
-        cs_s[t0] = in ? p.cs[((b * p.H + h) * p.nC + c) * p.Q + t0] : 0.f;
-        dt_s[t0] = in ? load_dt<T>(p, (b * p.T + c0 + t0) * p.H + h, h) : 0.f;
-        q_s[t0] = (p.seq_idx && in) ? p.seq_idx[c0 + t0] : 0;
+    {
+        const bool in = tid < L;
+        cs_s[tid] = in ? p.cs[((b * p.H + h) * p.nC + c) * p.Q + tid] : 0.f;
+        dt_s[tid] = in ? load_dt<T>(p, (b * p.T + c0 + tid) * p.H + h, h) : 0.f;
+        q_s[tid] = (p.seq_idx && in) ? p.seq_idx[c0 + tid] : 0;
     }
-    __syncthreads();
+    for (int z = blockIdx.x % split; z < nz; z += split) {
+        const int turn = (wave + h + c) & 3;
+        const int i = turn == 0 ? z : turn == 1 ? 2 * nz - 1 - z : turn == 2 ? 2 * nz + z : 4 * nz - 1 - z;
+        const int t = 16 * i + r;
+        const bool mine = i < nq && 16 * i < L;          // (uniform) this wavefront has a strip
+        const int last = 16 * (4 * nz - 1 - z) + 15;     // the workgroup's last token
+        const int send = last < L ? last + 1 : L;
+        __syncthreads();   // the chunk's scalars are in place (and the previous strips' reads done)
+        const float cst = t < kMaxQ ? cs_s[t] : 0.f;
+        const int qt = t < kMaxQ ? q_s[t] : 0;
 
-    f32x4_t acc[kMaxStrips][kMaxPT];
+        f32x4_t y[PT];
 #pragma unroll
-    for (int si = 0; si < kMaxStrips; ++si)
-#pragma unroll
-        for (int pt = 0; pt < kMaxPT; ++pt) acc[si][pt] = zero4();
+        for (int pt = 0; pt < PT; ++pt) y[pt] = zero4();
 
-    // diagonal block: Y^T[p][t] = sum_s x^T[p][s] * (G[t][s] L_ts dt_s)
-    for (int s0 = 0; s0 < L; s0 += kSlab) {
-        for (int idx = threadIdx.x; idx < kSlab * P; idx += kThreads) {
-            const int ss = idx / P, pp = idx % P, s = s0 + ss;
-            xT[pp * kPad + ss] = (s < L) ? Act<T>::load(xp, ((b * p.T + c0 + s) * p.H + h) * p.P + pp) : 0.f;
-        }
-        __syncthreads();
+        // diagonal block: Y^T[p][t] = sum_s x^T[p][s] * (G[t][s] L_ts dt_s)
+        for (int s0 = 0; s0 < send; s0 += kSlab) {
+            constexpr int kPieces = kSlab * P / 4, kPer = (kPieces + kThreads - 1) / kThreads;
+            f32x4_t vx[kPer];
 #pragma unroll
-        for (int si = 0; si < kMaxStrips; ++si) {
-            const int i = wave + 4 * si;
-            if (i < nq && 16 * i + 15 >= s0) {
-                const int t = 16 * i + r;
-                Frag8 fb;
+            for (int k = 0; k < kPer; ++k) {
+                const int e = tid + kThreads * k, s = s0 + e / (P / 4), f = 4 * (e % (P / 4));
+                vx[k] = zero4();
+                if (e < kPieces && s < L) vx[k] = load4(xp + s * xrow + f);
+            }
+            if (s0 > 0) __syncthreads();   // the previous slab's reads are done
 #pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    const int s = s0 + 8 * lg + e;
-                    const bool on = (s <= t) && (t < L) && (q_s[s] == q_s[t]);
-                    fb.v[e] = on ? Gp[t * p.Q + s] * exp2f(cs_s[t] - cs_s[s]) * dt_s[s] : 0.f;
-                }
+            for (int k = 0; k < kPer; ++k) {
+                const int e = tid + kThreads * k;
+                if (e < kPieces) *reinterpret_cast<f32x4_t*>(&xs[(e / (P / 4)) * XS + 4 * (e % (P / 4))]) = vx[k];
+            }
+            __syncthreads();
+            if (mine) {
+                const float* grow = Gp + t * p.Q + s0 + 4 * lg;
+                const int nj = min(kSlab / 16, i - s0 / 16 + 1);   // (may be <= 0: the strip ends before the slab)
+                for (int j = 0; j < nj; ++j) {
+                    const f32x4_t gv = *reinterpret_cast<const f32x4_t*>(grow + 16 * j);
+                    const int s = s0 + 16 * j + 4 * lg;
+                    const f32x4_t csv = *reinterpret_cast<const f32x4_t*>(&cs_s[s]);
+                    const f32x4_t dtv = *reinterpret_cast<const f32x4_t*>(&dt_s[s]);
+                    float m[4];
 #pragma unroll
-                for (int pt = 0; pt < kMaxPT; ++pt) {
-                    if (pt < TP) {
-                        Frag8 fa;
-#pragma unroll
-                        for (int e = 0; e < 8; ++e) fa.v[e] = xT[(16 * pt + r) * kPad + 8 * lg + e];
-                        acc[si][pt] = mma_step(fa, fb, acc[si][pt], T());
+                    for (int v = 0; v < 4; ++v) {
+                        const bool on = s + v <= t && t < L && (!p.seq_idx || q_s[s + v] == qt);
+                        m[v] = on ? gv[v] * exp2f(cst - csv[v]) * dtv[v] : 0.f;
                     }
+                    const float* xr = &xs[(16 * j + 4 * lg) * XS + r];
+#pragma unroll
+                    for (int v = 0; v < 4; ++v)
+#pragma unroll
+                        for (int pt = 0; pt < PT; ++pt) y[pt] = mma4(xr[v * XS + 16 * pt], m[v], y[pt]);
                 }
             }
         }
-        __syncthreads();
-    }
 
-    // left factors: per segment, Y^T[p][t] += scale_t * sum_n hin[p][n] C_t[n]
-    int st = 0;
-    while (st < L) {
-        int en = st;
-        while (en + 1 < L && q_s[en + 1] == q_s[st]) ++en;
-        const int q = q_s[st];
-        const bool cont = (st == 0) && (c == 0 || !p.seq_idx || p.seq_idx[c0 - 1] == q);
-        const float* hin = cont ? p.states + ((b * p.nC + c) * p.H + h) * PN
-                                : (p.init && unit_ok(p, q) ? p.init + (static_cast<int64_t>(q) * p.H + h) * PN : nullptr);
-        const float base = (st > 0) ? cs_s[st - 1] : 0.f;
-        if (hin) {
+        // left factors: per segment, Y^T[p][t] += scale_t * sum_n hin[p][n] C_t[n]
+        const T* ct = Cp + static_cast<int64_t>(t < L ? t : L - 1) * crow + 4 * lg;
+        int st = 0;
+        while (st < send) {
+            int en = L - 1;
+            if (p.seq_idx) {
+                en = st;
+                while (en + 1 < L && q_s[en + 1] == q_s[st]) ++en;
+            }
+            const int q = q_s[st];
+            const bool cont = (st == 0) && (c == 0 || !p.seq_idx || p.seq_idx[c0 - 1] == q);
+            const float* hin = cont ? p.states + ((b * p.nC + c) * p.H + h) * PN
+                                    : (p.init && unit_ok(p, q) ? p.init + (static_cast<int64_t>(q) * p.H + h) * PN : nullptr);
+            const float base = (st > 0) ? cs_s[st - 1] : 0.f;
+            if (hin) {
+                const bool reach = mine && 16 * i + 15 >= st && 16 * i <= en;
+                f32x4_t tmp[PT];
 #pragma unroll
-            for (int si = 0; si < kMaxStrips; ++si) {
-                const int i = wave + 4 * si;
-                if (i < nq && 16 * i + 15 >= st && 16 * i <= en) {
-                    const int t = 16 * i + r;
-                    const float scale = (t >= st && t <= en) ? exp2f(cs_s[t] - base) : 0.f;
+                for (int pt = 0; pt < PT; ++pt) tmp[pt] = zero4();
+                for (int n0 = 0; n0 < N; n0 += kNB) {
+                    constexpr int kPieces = P * kNB / 4, kPer = kPieces / kThreads;
+                    static_assert(kPer * kThreads == kPieces, "even split");
+                    f32x4_t vh[kPer];
 #pragma unroll
-                    for (int pt = 0; pt < kMaxPT; ++pt) {
-                        if (pt < TP) {
-                            f32x4_t tmp = zero4();
-                            for (int k0 = 0; k0 < N; k0 += 32) {
-                                Frag8 fa, fb;
+                    for (int k = 0; k < kPer; ++k) {
+                        const int e = tid + kThreads * k, f = 4 * (e % (kNB / 4));
+                        vh[k] = zero4();
+                        if (n0 + f < N) vh[k] = load4(hin + (e / (kNB / 4)) * N + n0 + f);
+                    }
+                    __syncthreads();   // the previous block's reads are done
 #pragma unroll
-                                for (int e = 0; e < 8; ++e) {
-                                    const int n = k0 + 8 * lg + e;
-                                    fa.v[e] = (n < N) ? hin[(16 * pt + r) * N + n] : 0.f;
-                                    fb.v[e] = (n < N && t < L) ? Act<T>::load(Cp, ((b * p.T + c0 + t) * p.G + g) * p.N + n) : 0.f;
-                                }
-                                tmp = mma_step(fa, fb, tmp, T());
+                    for (int k = 0; k < kPer; ++k) {
+                        const int e = tid + kThreads * k;
+                        *reinterpret_cast<f32x4_t*>(&hs[(e / (kNB / 4)) * HS + 4 * (e % (kNB / 4))]) = vh[k];
+                    }
+                    __syncthreads();
+                    if (reach) {
+                        const int nk = min(kNB, N - n0) / 16;
+                        for (int k = 0; k < nk; ++k) {
+                            const f32x4_t cv = load4(ct + n0 + 16 * k);
+#pragma unroll
+                            for (int pt = 0; pt < PT; ++pt) {
+                                const f32x4_t hv =
+                                    *reinterpret_cast<const f32x4_t*>(&hs[(16 * pt + r) * HS + 16 * k + 4 * lg]);
+#pragma unroll
+                                for (int v = 0; v < 4; ++v) tmp[pt] = mma4(hv[v], cv[v], tmp[pt]);
                             }
-#pragma unroll
-                            for (int v = 0; v < 4; ++v) acc[si][pt][v] += scale * tmp[v];
                         }
                     }
                 }
-            }
-        }
-        st = en + 1;
-    }
-
-    // skip term and store
-    const float Dh = p.D ? p.D[h] : 0.f;
-    T* yp = static_cast<T*>(p.y);
+                const float scale = (t >= st && t <= en) ? exp2f(cst - base) : 0.f;
 #pragma unroll
-    for (int si = 0; si < kMaxStrips; ++si) {
-        const int i = wave + 4 * si;
-        const int t = 16 * i + r;
-        if (i < nq && t < L) {
+                for (int pt = 0; pt < PT; ++pt) {
+                    settle(tmp[pt]);
+                    settle(y[pt]);
 #pragma unroll
-            for (int pt = 0; pt < kMaxPT; ++pt) {
-                if (pt < TP) {
-#pragma unroll
-                    for (int v = 0; v < 4; ++v) {
-                        const int pp = 16 * pt + 4 * lg + v;
-                        const int64_t o = ((b * p.T + c0 + t) * p.H + h) * p.P + pp;
-                        Act<T>::store(yp, o, acc[si][pt][v] + Dh * Act<T>::load(xp, o));
-                    }
+                    for (int v = 0; v < 4; ++v) y[pt][v] += scale * tmp[pt][v];
                 }
+            }
+            st = en + 1;
+        }
+
+        // skip term and store
+        if (mine && t < L) {
+            const float Dh = p.D ? p.D[h] : 0.f;
+            T* yp = static_cast<T*>(p.y) + ((b * p.T + c0 + t) * p.H + h) * P + 4 * lg;
+#pragma unroll
+            for (int pt = 0; pt < PT; ++pt) {
+                const f32x4_t xv = load4(xp + t * xrow + 16 * pt + 4 * lg);
+                settle(y[pt]);
+#pragma unroll
+                for (int v = 0; v < 4; ++v) y[pt][v] += Dh * xv[v];
+                store4(yp + 16 * pt, y[pt]);
             }
         }
     }
@@ -437,22 +582,38 @@ template <typename T>
 hipError_t launch_all(const Params& p, hipStream_t stream, hipEvent_t ev_begin, hipEvent_t ev_end)
 {
     const dim3 blk(kThreads);
-    const dim3 g_chunk(static_cast<unsigned>(p.nC), static_cast<unsigned>(p.H), static_cast<unsigned>(p.b));
-    const dim3 g_gram(static_cast<unsigned>(p.nC), static_cast<unsigned>(p.G), static_cast<unsigned>(p.b));
+    const unsigned H = static_cast<unsigned>(p.H), nb = static_cast<unsigned>(p.b);
+    const dim3 g_chunk(static_cast<unsigned>(p.nC), H, nb);
+    // workgroups per chunk (one when that many chunks already fill the grid's range)
+    const auto split = [&](int64_t parts) { return static_cast<int>(p.nC * parts <= (1 << 23) ? parts : 1); };
+    const int nq = static_cast<int>(p.Q / 16);
+    const int sp_gram = split(nq), sp_state = split(state_tiles(p.P, p.N)), sp_out = split(nq >= 4 ? nq / 4 : 1);
+    const dim3 g_gram(static_cast<unsigned>(p.nC * sp_gram), static_cast<unsigned>(p.G), nb);
+    const dim3 g_state(static_cast<unsigned>(p.nC * sp_state), H, nb);
+    const dim3 g_out(static_cast<unsigned>(p.nC * sp_out), H, nb);
     const dim3 g_scan(static_cast<unsigned>((p.P * p.N + kThreads - 1) / kThreads),
                       static_cast<unsigned>(p.H), static_cast<unsigned>(p.b));
     hipLaunchKernelGGL(k_chunk_prep<T>, g_chunk, blk, 0, stream, p);
-    hipLaunchKernelGGL(k_gram<T>, g_gram, blk, 0, stream, p);
-    hipLaunchKernelGGL(k_chunk_state<T>, g_chunk, blk, 0, stream, p);
+    hipLaunchKernelGGL(k_gram<T>, g_gram, blk, 0, stream, p, sp_gram);
+    hipLaunchKernelGGL(k_chunk_state<T>, g_state, blk, 0, stream, p, sp_state);
     hipLaunchKernelGGL(k_state_scan, g_scan, blk, 0, stream, p);
     hipError_t err = hipGetLastError();
     if (err == hipSuccess && ev_begin) err = hipEventRecord(ev_begin, stream);
     if (err != hipSuccess) return err;
-    hipLaunchKernelGGL(k_chunk_output<T>, g_chunk, blk, 0, stream, p);
+    switch (p.P / 16) {
+    case 1: hipLaunchKernelGGL((k_chunk_output<T, 1>), g_out, blk, 0, stream, p, sp_out); break;
+    case 2: hipLaunchKernelGGL((k_chunk_output<T, 2>), g_out, blk, 0, stream, p, sp_out); break;
+    case 3: hipLaunchKernelGGL((k_chunk_output<T, 3>), g_out, blk, 0, stream, p, sp_out); break;
+    case 4: hipLaunchKernelGGL((k_chunk_output<T, 4>), g_out, blk, 0, stream, p, sp_out); break;
+    case 5: hipLaunchKernelGGL((k_chunk_output<T, 5>), g_out, blk, 0, stream, p, sp_out); break;
+    case 6: hipLaunchKernelGGL((k_chunk_output<T, 6>), g_out, blk, 0, stream, p, sp_out); break;
+    case 7: hipLaunchKernelGGL((k_chunk_output<T, 7>), g_out, blk, 0, stream, p, sp_out); break;
+    default: hipLaunchKernelGGL((k_chunk_output<T, 8>), g_out, blk, 0, stream, p, sp_out); break;
+    }
     err = hipGetLastError();
     if (err == hipSuccess && ev_end) err = hipEventRecord(ev_end, stream);
     if (err != hipSuccess) return err;
-    if (p.seq_idx && p.fin) hipLaunchKernelGGL(k_varlen_final<T>, g_chunk, blk, 0, stream, p);
+    if (p.seq_idx && p.fin) hipLaunchKernelGGL(k_varlen_final<T>, g_state, blk, 0, stream, p, sp_state);
     return hipGetLastError();
 }
 
