@@ -617,7 +617,8 @@ int backward_plan(const ssd_problem* prob, ssd::BwdParams* p, ssd::BwdLayout* l,
     p->nC = (s.T + Q - 1) / Q;
     if (static_cast<double>(p->b) * p->nC * p->H * p->P * p->N > 16.0 * ssd::kMaxElemsPublic)
         return SSD_ERR_TOO_LARGE;
-    ssd::bwd_slices(p->b, p->nC, p->G, p->H / p->G, &p->S, &p->hs);
+    // (the general path's dB / dC kernel takes 64 state columns a workgroup)
+    ssd::bwd_slices(p->b, p->nC, *fast ? p->G : p->G * ((p->N + 63) / 64), p->H / p->G, &p->S, &p->hs);
     if (const int64_t v = ssd::tuning(ssd::kTuneBwdHeadsPerSlice); v >= 1) {
         p->hs = v < p->H / p->G ? v : p->H / p->G;
         p->S = (p->H / p->G + p->hs - 1) / p->hs;
@@ -665,6 +666,9 @@ int backward_impl(const ssd_problem* prob, const void* x, const void* dt, const 
     p.dD = D ? dD : nullptr;
     p.dinit = dinitial_states;
     p.cs = fast ? nullptr : reinterpret_cast<float*>(ws + l.cs);
+    p.gram = fast ? nullptr : reinterpret_cast<float*>(ws + l.gram);
+    p.q1p = fast ? nullptr : reinterpret_cast<float*>(ws + l.q1p);
+    p.ghp = fast ? nullptr : reinterpret_cast<float*>(ws + l.ghp);
     p.hin = reinterpret_cast<float*>(ws + l.hin);
     p.gn = fast ? nullptr : reinterpret_cast<float*>(ws + l.gn);
     p.gnT = fast ? reinterpret_cast<float*>(ws + l.gnT) : nullptr;

@@ -109,58 +109,6 @@ __device__ __forceinline__ uint4 ldfrag_g(const u16* a, int64_t ld, int row, int
     return *reinterpret_cast<const uint4*>(a + static_cast<int64_t>(row) * ld + ks * 32 + 8 * (lane >> 4));
 }
 
-// Cross-lane sums in registers (DPP and the permlane swaps; no trip through
-// shared memory).
-template <int CTRL, int ROWS>
-__device__ __forceinline__ float dpp(float v)
-{
-    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, ROWS, 0xF, false));
-}
-
-// Sum over the 16 lanes of each row (row_ror by 8, 4, 2, 1): every lane of the row gets it.
-__device__ __forceinline__ float row_sum16(float v)
-{
-    v += dpp<0x128, 0xF>(v);
-    v += dpp<0x124, 0xF>(v);
-    v += dpp<0x122, 0xF>(v);
-    v += dpp<0x121, 0xF>(v);
-    return v;
-}
-
-// Sum over the four rows at each position (lanes r, r + 16, r + 32, r + 48):
-// swapping odd rows with even ones, then the halves, and adding.
-__device__ __forceinline__ float col_sum4(float v)
-{
-    uint32_t u = __float_as_uint(v);
-    const auto a = __builtin_amdgcn_permlane16_swap(u, u, false, false);
-    v = __uint_as_float(a[0]) + __uint_as_float(a[1]);
-    u = __float_as_uint(v);
-    const auto b = __builtin_amdgcn_permlane32_swap(u, u, false, false);
-    return __uint_as_float(b[0]) + __uint_as_float(b[1]);
-}
-
-// Sum over the 64 lanes of a wavefront (every lane gets it).
-__device__ __forceinline__ float wave_sum(float v) { return col_sum4(row_sum16(v)); }
-
-// Inclusive prefix sum over the 64 lanes: shifts by 1, 2, 4, 8 within each
-// row, then the row totals carried up by broadcasts of lanes 15 (into rows 1
-// and 3) and 31 (into rows 2 and 3).  Lanes with no source add zero.
-__device__ __forceinline__ float wave_scan(float v)
-{
-    v += dpp<0x111, 0xF>(v);
-    v += dpp<0x112, 0xF>(v);
-    v += dpp<0x114, 0xF>(v);
-    v += dpp<0x118, 0xF>(v);
-    v += dpp<0x142, 0xA>(v);
-    v += dpp<0x143, 0xC>(v);
-    return v;
-}
-
-__device__ __forceinline__ float lane_value(float v, int lane)
-{
-    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), lane));
-}
-
 __device__ __forceinline__ int chunk_len2(int64_t T, int64_t c)
 {
     const int64_t r = T - c * kQ2;

@@ -9,9 +9,9 @@
 namespace ssd {
 
 // Tokens per chunk of the backward's own decomposition (independent of the
-// forward's chunk size: the gradient of the layer does not depend on it):
-// 32 on the general path, 64 on the matrix-core path.
-constexpr int64_t kBwdQ = 32;
+// forward's chunk size: the gradient of the layer does not depend on it), on
+// the general path and on the bf16 matrix-core path.
+constexpr int64_t kBwdQ = 64;
 constexpr int64_t kBwdQFast = 64;
 
 struct BwdParams {
@@ -34,8 +34,12 @@ struct BwdParams {
     float* dD;             // may be null
     float* dinit;          // may be null
     // workspace (float32)
-    float* cs;     // (b, H, nC, kBwdQ)   chunk-local inclusive cumsum of dt*A, log2 units
-                   //                     (general path only)
+    // general path only:
+    float* cs;     // (b, H, nC)          each chunk's decay, exp(its sum of dt A)
+    float* gram;   // (b, G, nC, t, u)    C_u . B_t (u-tile >= t-tile)
+    float* q1p;    // (N / 64, b, H, T)   dy_u . (h_in C_u) over 64 state columns
+    float* ghp;    // (N / 64, b, H, nC)  <Gn, h_in> over 64 state columns
+    // both paths:
     float* hin;    // (b, nC, H, P, N)    chunk states, then the state entering each chunk
                    //                     (matrix-core path: bf16, (b, nC, H, N, P))
     float* gn;     // (b, nC, H, P, N)    output-to-state terms, then the gradient of the state
@@ -61,7 +65,7 @@ struct BwdParams {
 };
 
 struct BwdLayout {
-    size_t cs, hin, gn, gnT, dBp, dCp, dAp, dDp, total;
+    size_t cs, hin, gn, gnT, gram, q1p, ghp, dBp, dCp, dAp, dDp, total;
 };
 
 // Head slices: enough (b, chunk, group, slice) workgroups to fill the chip.

@@ -30,53 +30,6 @@ constexpr int kMaxQ = 256;
 constexpr int kSlab = 64;      // tokens of x (and B) staged in LDS at a time
 constexpr int kNB = 64;        // state columns staged in LDS at a time
 
-// Four consecutive activations as floats.  Rows are multiples of 16 elements,
-// but the caller's pointers need only be aligned to their own type, so the
-// vectors say so (the hardware reads and writes them at any alignment).
-typedef float f4u_t __attribute__((ext_vector_type(4), aligned(4)));
-typedef uint16_t h4u_t __attribute__((ext_vector_type(4), aligned(2)));
-
-__device__ __forceinline__ f32x4_t load4(const float* p)
-{
-    const f4u_t v = *reinterpret_cast<const f4u_t*>(p);
-    return f32x4_t{v.x, v.y, v.z, v.w};
-}
-
-__device__ __forceinline__ f32x4_t load4(const uint16_t* p)
-{
-    const h4u_t v = *reinterpret_cast<const h4u_t*>(p);
-    f32x4_t f;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) f[e] = __uint_as_float(static_cast<uint32_t>(v[e]) << 16);
-    return f;
-}
-
-__device__ __forceinline__ void store4(float* p, f32x4_t v) { *reinterpret_cast<f4u_t*>(p) = f4u_t{v[0], v[1], v[2], v[3]}; }
-
-__device__ __forceinline__ void store4(uint16_t* p, f32x4_t v)
-{
-    h4u_t h;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        uint16_t u;
-        Act<uint16_t>::store(&u, 0, v[e]);   // round to nearest even
-        h[e] = u;
-    }
-    *reinterpret_cast<h4u_t*>(p) = h;
-}
-
-// One float32 matrix instruction: D[4 g + v][r] += sum over the lane groups
-// g' = 0..3 of A (row r of the lane) x B (column r of the lane).
-__device__ __forceinline__ f32x4_t mma4(float a, float b, f32x4_t c)
-{
-    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
-}
-
-// Sixteen wait states between matrix instructions of a loop with a run-time
-// trip count and the first read of their results after it (the compiler has
-// been seen to leave too few on one path out of such a loop).
-__device__ __forceinline__ void settle(f32x4_t& a) { asm volatile("s_nop 15" : "+v"(a)); }
-
 // Sequence ids outside [0, nseq) break the seq_idx contract; state reads and
 // writes for them are skipped so that such input cannot fault the device.
 __device__ __forceinline__ bool unit_ok(const Params& p, int64_t u)
