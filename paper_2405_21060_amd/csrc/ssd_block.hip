@@ -11,6 +11,8 @@
 // `group` channels is `group / 8` pieces of 8 channels (one 16- or 32-byte
 // vector); `seg` lanes (a power of two, at most 64) share a group and reduce
 // its sum with shuffles inside their segment; a wavefront holds 64 / seg groups.
+// Groups of more than 128 pieces (the whole row of a layer with one group) take
+// a workgroup each (k_gate_norm_wide).
 #include "ssd_device.h"
 #include "ssd_internal.h"
 
@@ -66,6 +68,14 @@ struct Vec8<float> {
 };
 
 __device__ __forceinline__ float silu_f(float z) { return z / (1.f + expf(-z)); }
+
+// The same by v_exp_f32 and v_rcp_f32 (1 ulp each), for results that are rounded
+// to bf16 (as in the fused chunk kernel's output stage); z of large magnitude
+// gives 0 or z, as above.
+__device__ __forceinline__ float silu_fast(float z)
+{
+    return z * __builtin_amdgcn_rcpf(1.f + __builtin_amdgcn_exp2f(-z * kLog2e));
+}
 
 // Gated piece: y, times SiLU(z) when gating.
 template <typename T>
@@ -160,6 +170,58 @@ __global__ __launch_bounds__(kGateNormThreads) void k_gate_norm(GateNormParams p
     }
 }
 
+// Gate (optional) and RMS normalisation of groups wider than 128 pieces, one
+// workgroup of up to 512 threads per (row, group) and K (1 or 2) pieces per
+// thread, all loads of y and z in flight at once, one sum over the workgroup.
+// Memory-bound: reads y and z and writes y once.  At 16,384 rows of 5,120
+// channels, bf16, one group: 92 us for 503 MB, where one wavefront per group
+// (ten pieces a lane, 84 registers) took 149; with the full-precision division
+// and exponential in the gate 109 us (the vector unit bounds it then).
+template <typename T, int K>
+__global__ __launch_bounds__(512) void k_gate_norm_wide(GateNormParams p)
+{
+    __shared__ float part[2][8];
+    const int64_t gpr = p.C / p.group, ngroups = p.rows * gpr;
+    const int pieces = static_cast<int>(p.group / 8), tid = threadIdx.x, nt = blockDim.x;
+    int slot = 0;
+    for (int64_t gid = blockIdx.x; gid < ngroups; gid += gridDim.x, slot ^= 1) {
+        const int64_t row = gid / gpr, c0 = (gid - row * gpr) * p.group, base = row * p.C + c0;
+        float g[K][8], zv[K][8];
+#pragma unroll
+        for (int k = 0; k < K; ++k)
+            if (tid + k * nt < pieces) {
+                Vec8<T>::load(static_cast<const T*>(p.y), base + 8 * (tid + k * nt), g[k]);
+                if (p.z) Vec8<T>::load(static_cast<const T*>(p.z), base + 8 * (tid + k * nt), zv[k]);
+            }
+        float ss = 0.f;
+#pragma unroll
+        for (int k = 0; k < K; ++k)
+            if (tid + k * nt < pieces)
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    if (p.z) g[k][e] *= sizeof(T) == 2 ? silu_fast(zv[k][e]) : silu_f(zv[k][e]);
+                    ss += g[k][e] * g[k][e];
+                }
+        ss = wave_sum(ss);
+        if ((tid & 63) == 0) part[slot][tid >> 6] = ss;
+        __syncthreads();   // (the other slot is rewritten only after the next group's barrier)
+        float tot = 0.f;
+        for (int w = 0; w < nt / 64; ++w) tot += part[slot][w];
+        const float scale = 1.f / sqrtf(tot / static_cast<float>(p.group) + p.eps);
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            const int j = tid + k * nt;
+            if (j < pieces) {
+                float wv[8];
+                if (p.weight) Vec8<float>::load(p.weight, c0 + 8 * j, wv);
+#pragma unroll
+                for (int e = 0; e < 8; ++e) g[k][e] = p.weight ? g[k][e] * scale * wv[e] : g[k][e] * scale;
+                Vec8<T>::store(static_cast<T*>(p.y), base + 8 * j, g[k]);
+            }
+        }
+    }
+}
+
 }  // namespace
 
 hipError_t launch_gate_norm(const GateNormParams& p, bool bf16, hipStream_t stream)
@@ -175,6 +237,20 @@ hipError_t launch_gate_norm(const GateNormParams& p, bool bf16, hipStream_t stre
         return hipGetLastError();
     }
     const int64_t pieces = p.group / 8;
+    // Wide groups: a workgroup each.  Up to 128 pieces one wavefront holds the
+    // group in two pieces a lane.
+    if (pieces > 128 && pieces <= 1024) {
+        const int k = pieces > 512 ? 2 : 1;
+        const unsigned threads = static_cast<unsigned>(((pieces + k - 1) / k + 63) / 64 * 64);
+        const int64_t wgroups = p.rows * (p.C / p.group), most = 1 << 22;   // (512 threads each: the grid's range)
+        const dim3 grid(static_cast<unsigned>(wgroups < most ? wgroups : most));
+        const auto go = [&](auto kern) { hipLaunchKernelGGL(kern, grid, dim3(threads), 0, stream, p); };
+        if (bf16)
+            k == 1 ? go(k_gate_norm_wide<uint16_t, 1>) : go(k_gate_norm_wide<uint16_t, 2>);
+        else
+            k == 1 ? go(k_gate_norm_wide<float, 1>) : go(k_gate_norm_wide<float, 2>);
+        return hipGetLastError();
+    }
     int seg = 1, log2seg = 0;
     while (seg < pieces && seg < 64) {
         seg <<= 1;
@@ -190,14 +266,10 @@ hipError_t launch_gate_norm(const GateNormParams& p, bool bf16, hipStream_t stre
     if (bf16) {
         if (per_lane <= 1) go(k_gate_norm<uint16_t, 1>);
         else if (per_lane <= 2) go(k_gate_norm<uint16_t, 2>);
-        else if (per_lane <= 4) go(k_gate_norm<uint16_t, 4>);
-        else if (per_lane <= 16) go(k_gate_norm<uint16_t, 16>);
         else go(k_gate_norm<uint16_t, 0>);
     } else {
         if (per_lane <= 1) go(k_gate_norm<float, 1>);
         else if (per_lane <= 2) go(k_gate_norm<float, 2>);
-        else if (per_lane <= 4) go(k_gate_norm<float, 4>);
-        else if (per_lane <= 16) go(k_gate_norm<float, 16>);
         else go(k_gate_norm<float, 0>);
     }
     return hipGetLastError();
