@@ -12,9 +12,10 @@
 //                  tiles (u >= t) R0 = dy x^T and G0 = C B^T (once per
 //                  workgroup), then dX~^T = dy^T Gs + Gn B^T, dB^T = C^T Rs +
 //                  Gn^T x~^T, dC^T = B^T Rs^T + h_in^T dy^T, each as 16 x 16
-//                  tiles whose operands are k-contiguous rows: in shared memory
-//                  (B, B^T, C^T, x, dy, dy^T, the score tiles and Gn, transposed
-//                  there from Gn^T), or straight from global memory (Gn^T, h_in^T).
+//                  tiles.  B, Gn^T, x, dy and the scores lie in shared memory
+//                  once, as they come, and are read by rows or transposed
+//                  (ds_read_b64_tr_b16); what every head takes of C^T and B^T is
+//                  in registers, h_in^T comes straight from global memory.
 //
 // H32 (a template flag; the block gradients use it): dt and dy come in as
 // float32 and ddt goes out as float32.  dy is rounded to bf16 only where it is
@@ -23,8 +24,9 @@
 // An MFMA operand row holds the contraction index contiguously; a lane
 // (row r = lane % 16, group q = lane / 16) reads 8 of them (k = 32 s + 8 q ..
 // + 7) as one 16-byte load, and the result tile D[4 q + v][r] lands in its
-// four accumulator registers.  Shared arrays are padded by 8 elements per
-// row so that the 16 rows of a fragment read fall in distinct banks.
+// four accumulator registers.  A transposing read gives slots 0..3 k = 32 s +
+// 4 q .. + 3 and slots 4..7 k = 32 s + 16 + 4 q .. + 3 ("slot order"): the other
+// operand of such a product is stored in that order.
 #include <type_traits>
 
 #include "ssd_bwd.h"
@@ -36,9 +38,10 @@ namespace {
 constexpr int kQ2 = 64;          // tokens per chunk
 constexpr int kP2 = 64;          // head dimension
 constexpr int kT2 = 512;         // threads per workgroup (8 wavefronts)
-constexpr int kLd = kQ2 + 8;     // row stride (elements) of 64-wide shared rows
 
 typedef uint16_t u16;
+typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
+typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ bf16x8_t frag(uint4 v) { return __builtin_bit_cast(bf16x8_t, v); }
 
@@ -47,48 +50,20 @@ __device__ __forceinline__ f32x4_t mma(uint4 a, uint4 b, f32x4_t c)
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(frag(a), frag(b), c, 0, 0, 0);
 }
 
-__device__ __forceinline__ uint32_t bf16_bits(float f)
+// Two floats rounded to bf16 (nearest even, one v_cvt_pk_bf16_f32), the first in
+// the low half.
+__device__ __forceinline__ uint32_t pack2(float lo, float hi)
 {
-    uint32_t u = __float_as_uint(f);
-    return (u + 0x7FFFu + ((u >> 16) & 1u)) >> 16;   // nearest even (finite inputs)
+    typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
+    bf16x2_t v;
+    v[0] = static_cast<__bf16>(lo);
+    v[1] = static_cast<__bf16>(hi);
+    return __builtin_bit_cast(uint32_t, v);
 }
 
-__device__ __forceinline__ uint32_t pack2(float lo, float hi) { return bf16_bits(lo) | (bf16_bits(hi) << 16); }
+__device__ __forceinline__ uint32_t bf16_bits(float f) { return pack2(f, 0.f) & 0xFFFFu; }
 
-__device__ __forceinline__ float bf(u16 v) { return __uint_as_float(static_cast<uint32_t>(v) << 16); }
-
-// Two floats rounded to bf16 (nearest even; the inputs are finite), the first
-// in the low half.
-__device__ __forceinline__ uint32_t rne_pair(float a, float b)
-{
-    uint32_t ua = __float_as_uint(a), ub = __float_as_uint(b);
-    ua += 0x7FFFu + ((ua >> 16) & 1u);
-    ub += 0x7FFFu + ((ub >> 16) & 1u);
-    return (ua >> 16) | (ub & 0xFFFF0000u);
-}
-
-// dt of token row i (bf16 bits, or float32 with H32).
-template <bool H32>
-__device__ __forceinline__ float load_dt(const void* dt, int64_t i)
-{
-    if constexpr (H32)
-        return static_cast<const float*>(dt)[i];
-    else
-        return bf(static_cast<const u16*>(dt)[i]);
-}
-
-// dt as raw bits (float32, or bf16 in the low half), widened where it is used:
-// a load whose value is converted at once makes the wavefront wait for every
-// memory operation issued before it (the prefetches and the state stores).
-template <bool H32>
-__device__ __forceinline__ uint32_t load_dt_raw(const void* dt, int64_t i)
-{
-    if constexpr (H32)
-        return __float_as_uint(static_cast<const float*>(dt)[i]);
-    else
-        return static_cast<const u16*>(dt)[i];
-}
-
+// dt from its raw bits (float32, or bf16 in the low half).
 template <bool H32>
 __device__ __forceinline__ float dt_of_raw(uint32_t v)
 {
@@ -97,17 +72,6 @@ __device__ __forceinline__ float dt_of_raw(uint32_t v)
 
 __device__ __forceinline__ float lo_f(uint32_t w) { return __uint_as_float(w << 16); }
 __device__ __forceinline__ float hi_f(uint32_t w) { return __uint_as_float(w & 0xFFFF0000u); }
-
-// One operand fragment of a row-major bf16 array: row `row`, k-step `ks`.
-__device__ __forceinline__ uint4 ldfrag(const u16* a, int ld, int row, int ks, int lane)
-{
-    return *reinterpret_cast<const uint4*>(a + row * ld + ks * 32 + 8 * (lane >> 4));
-}
-
-__device__ __forceinline__ uint4 ldfrag_g(const u16* a, int64_t ld, int row, int ks, int lane)
-{
-    return *reinterpret_cast<const uint4*>(a + static_cast<int64_t>(row) * ld + ks * 32 + 8 * (lane >> 4));
-}
 
 __device__ __forceinline__ int chunk_len2(int64_t T, int64_t c)
 {
@@ -225,9 +189,9 @@ __global__ __launch_bounds__(kPassT, H32 ? 2 : 1) void k_bwd2_pass(BwdParams p)
         constexpr int kXK = kQ2 * kP2 / 8 / kPassT;   // 2
         constexpr int kYK = kQ2 * N / 8 / kPassT;     // N / 32
         struct Stage {
-            uint32_t dt;   // raw bits (see load_dt_raw)
-            uint4 x[kXK], y[kYK];
-            float4 xf[H32 ? 2 * kXK : 1];   // H32, dir 1: dy in float32
+            uint32_t dt;   // raw bits (widened where used: a conversion waits for the loads before it)
+            u32x4_t x[kXK], y[kYK];
+            f32x4_t xf[H32 ? 2 * kXK : 1];   // H32, dir 1: dy in float32
         };
         int64_t first = 0, nch = p.nC;   // this row's (or sequence's) chunks
         if constexpr (PACKED) {
@@ -270,14 +234,14 @@ __global__ __launch_bounds__(kPassT, H32 ? 2 : 1) void k_bwd2_pass(BwdParams p)
                         const_cast<float*>(dyf) + (t0 * p.H + h) * kP2, 0,
                         ((L - 1) * xrow + kP2) * static_cast<int>(sizeof(float)), 0x00020000);
                     const int off = (s * xrow + f) * static_cast<int>(sizeof(float));
-                    st.xf[2 * kk] = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(rs, off, 0, 0));
-                    st.xf[2 * kk + 1] = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(rs, off + 16, 0, 0));
+                    st.xf[2 * kk] = __builtin_bit_cast(f32x4_t, __builtin_amdgcn_raw_buffer_load_b128(rs, off, 0, 0));
+                    st.xf[2 * kk + 1] = __builtin_bit_cast(f32x4_t, __builtin_amdgcn_raw_buffer_load_b128(rs, off + 16, 0, 0));
                 } else {
                     const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
                         const_cast<u16*>(src) + (t0 * p.H + h) * kP2, 0,
                         ((L - 1) * xrow + kP2) * static_cast<int>(sizeof(u16)), 0x00020000);
-                    st.x[kk] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(
-                                                             rs, (s * xrow + f) * static_cast<int>(sizeof(u16)), 0, 0));
+                    st.x[kk] = __builtin_amdgcn_raw_buffer_load_b128(
+                        rs, (s * xrow + f) * static_cast<int>(sizeof(u16)), 0, 0);
                 }
             }
             const int yrow = static_cast<int>(p.G) * N;   // elements between tokens of B (C)
@@ -287,8 +251,7 @@ __global__ __launch_bounds__(kPassT, H32 ? 2 : 1) void k_bwd2_pass(BwdParams p)
     #pragma unroll
             for (int kk = 0; kk < kYK; ++kk) {
                 const int i = tid + kPassT * kk, s = i / (N / 8), f = 8 * (i % (N / 8));
-                st.y[kk] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(
-                                                         ry, (s * yrow + f) * static_cast<int>(sizeof(u16)), 0, 0));
+                st.y[kk] = __builtin_amdgcn_raw_buffer_load_b128(ry, (s * yrow + f) * static_cast<int>(sizeof(u16)), 0, 0);
             }
         };
         const auto step = [&](Stage& st, int64_t k) {
@@ -306,7 +269,7 @@ __global__ __launch_bounds__(kPassT, H32 ? 2 : 1) void k_bwd2_pass(BwdParams p)
                 const float ws = __shfl(wt, s, 64);
                 uint32_t o[4];
                 if constexpr (S32) {
-                    const float4 a = st.xf[2 * kk], c2 = st.xf[2 * kk + 1];
+                    const f32x4_t a = st.xf[2 * kk], c2 = st.xf[2 * kk + 1];
                     o[0] = pack2(ws * a.x, ws * a.y);
                     o[1] = pack2(ws * a.z, ws * a.w);
                     o[2] = pack2(ws * c2.x, ws * c2.y);
@@ -321,7 +284,7 @@ __global__ __launch_bounds__(kPassT, H32 ? 2 : 1) void k_bwd2_pass(BwdParams p)
     #pragma unroll
             for (int kk = 0; kk < kYK; ++kk) {
                 const int i = tid + kPassT * kk, s = i / (N / 8), f = 8 * (i % (N / 8));
-                *reinterpret_cast<uint4*>(YS + tok_off<N>(s, f)) = st.y[kk];
+                *reinterpret_cast<u32x4_t*>(YS + tok_off<N>(s, f)) = st.y[kk];
             }
             fetch(st, k + 2);
 
@@ -377,28 +340,129 @@ __global__ __launch_bounds__(kPassT, H32 ? 2 : 1) void k_bwd2_pass(BwdParams p)
 }
 
 // ---------------------------------------------------------------------------
-// Chunk gradients.
-template <int N, bool H32 = false>
-struct ChunkSmem {
-    // Row strides (elements) of the shared tiles: N-wide rows (B, Gn) and
-    // 64-wide rows (the rest).  Padding spreads the 16 rows an operand read or
-    // a tile write touches over the banks; measured at the 2.7B shape (row
-    // strides 72 / N + 8 before): 80 / N + 16 0.885 ms per backward, 80 / N + 8
-    // 0.903, 88 / N + 8 0.935, 72 / N + 8 0.918.  With the float32 dy copy
-    // (H32) the 64-wide rows keep 72 elements so that it still fits.
-    static constexpr int kLdN = N + 16;
-    static constexpr int kLdC = H32 ? kLd : kLd + 8;
-    static constexpr int kLdF = kP2 + 4;   // row stride (floats) of the float32 dy copy (H32)
-    static constexpr size_t kBytes =
-        sizeof(u16) * (2 * static_cast<size_t>(kQ2) * kLdN + 2 * N * kLdC + 6 * kQ2 * kLdC) +
-        (H32 ? sizeof(float) * kQ2 * kLdF : 0);
+// Chunk gradients.  Shared arrays are rows of 16-byte groups XOR-swizzled by the
+// row (tok_off), each value once:
+//   Bs  64 x N   B (row t), with n in the order of the transposing reads' slots
+//                (perm_off): one 16-byte read is an operand of the products over n
+//   Gn  N x 64   Gn^T (row n), as it lies in memory; read by rows for the products
+//                over p and transposed for the one over n.  Holds C (64 x N) first.
+//   xs, dys  64 x 64   x and dy (row = token)
+//   Gs, Rs   64 x 64   the masked scores, row t, with u in the slots' order
+// Bound by the latency of its phases and the issue of vector and shared-memory
+// instructions (two wavefronts per SIMD), not by its bytes.  Transposed copies
+// of B, C, dy, Gn and the scores written element by element for every head,
+// software rounding, products over the zero half of the scores, and state loads
+// issued at the head that uses them took 564 us at the 2.7B shape (4 x 4,096
+// tokens, 80 heads); reading one copy transposed 467, with the states fetched a
+// head ahead 403.  (128 registers, two workgroups per compute unit: 1,455 us,
+// the operands fetched ahead are spilled.)
+template <int N>
+constexpr size_t chunk_smem()
+{
+    return sizeof(u16) * (2 * static_cast<size_t>(kQ2) * N + 4 * kQ2 * kP2);
+}
+
+// Element offset of column 32 m + 16 h + 4 g (+ 0..3) of row s in a buffer whose
+// columns lie in slot order: position 32 m + 8 g + 4 h.
+template <int F>
+__device__ __forceinline__ int perm_off(int s, int m, int h, int g)
+{
+    return tok_off<F>(s, 32 * m + 8 * g + 4 * h);
+}
+
+// Operand fragment of row `row`, k-step ks (eight consecutive positions).
+template <int F>
+__device__ __forceinline__ uint4 row_frag(const u16* buf, int row, int ks, int lane)
+{
+    return *reinterpret_cast<const uint4*>(buf + tok_off<F>(row, 32 * ks + 8 * (lane >> 4)));
+}
+
+// tr_frag of a buffer whose columns lie in slot order: columns 16 ft .. + 15.
+template <int F>
+__device__ __forceinline__ uint4 tr_frag_perm(const u16* buf, int m, int ft, int lane)
+{
+    const int j = lane & 15, g = lane >> 4, row = 32 * m + 4 * g + (j >> 2);
+    const uint2 lo = __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+                                                   (lds_v4i16*)(buf + perm_off<F>(row, ft >> 1, ft & 1, j & 3))));
+    const uint2 hi = __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+                                                   (lds_v4i16*)(buf + perm_off<F>(row + 16, ft >> 1, ft & 1, j & 3))));
+    return make_uint4(lo.x, lo.y, hi.x, hi.y);
+}
+
+// Four sums over the lane groups q at once: lane group q gets the sum of v_q
+// over lanes r, r + 16, r + 32, r + 48.
+__device__ __forceinline__ float col_sum4x4(float v0, float v1, float v2, float v3)
+{
+    const auto a = __builtin_amdgcn_permlane32_swap(__float_as_uint(v0), __float_as_uint(v2), false, false);
+    const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(v1), __float_as_uint(v3), false, false);
+    const float s = __uint_as_float(a[0]) + __uint_as_float(a[1]), t = __uint_as_float(b[0]) + __uint_as_float(b[1]);
+    const auto c = __builtin_amdgcn_permlane16_swap(__float_as_uint(s), __float_as_uint(t), false, false);
+    return __uint_as_float(c[0]) + __uint_as_float(c[1]);
+}
+
+// Four sums over the 16 lanes of a row at once: lane r gets the sum of v_(r % 4).
+__device__ __forceinline__ float row_sum16x4(float v0, float v1, float v2, float v3, int r)
+{
+    const bool o1 = r & 1, o2 = r & 2;
+    const float a = (o1 ? v1 : v0) + dpp<0xB1, 0xF>(o1 ? v0 : v1);
+    const float b = (o1 ? v3 : v2) + dpp<0xB1, 0xF>(o1 ? v2 : v3);
+    float c = (o2 ? b : a) + dpp<0x4E, 0xF>(o2 ? a : b);
+    c += dpp<0x124, 0xF>(c);
+    c += dpp<0x128, 0xF>(c);
+    return c;
+}
+
+// Byte offsets of a lane's accesses within the shared buffers (tile and k-step
+// add constants): rows of 64 and of N elements by k-step, the transposing reads
+// by tile pair (op) and of p-tile pw (ot), the lane's x and dy of a dX^T tile.
+// Each phase works them out from its own opaque copy of the lane: the compiler
+// would otherwise keep every sum with a tile's offset in a register of its own
+// across the heads (100 registers spilled).
+template <int N>
+struct LaneOffs {
+    int r, q, oa[2], ob[2], op[2], ot, ox;
+
+    __device__ __forceinline__ LaneOffs(int lane, int pw)
+    {
+        asm volatile("" : "+v"(lane));
+        r = lane & 15;
+        q = lane >> 4;
+        const int j4 = lane & 3, trow = 4 * q + (r >> 2);
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks) {
+            oa[ks] = 2 * tok_off<kP2>(r, 32 * ks + 8 * q);
+            ob[ks] = 2 * tok_off<N>(r, 32 * ks + 8 * q);
+            op[ks] = 2 * tok_off<kP2>(trow, 32 * ks + 8 * j4);
+        }
+        ot = 2 * tok_off<kP2>(trow, 16 * pw + 4 * j4);
+        ox = 2 * tok_off<kP2>(r, 16 * pw + 4 * q);
+    }
+    static __device__ __forceinline__ const char* at(const u16* buf, int off)
+    {
+        return reinterpret_cast<const char*>(buf) + off;
+    }
+    __device__ __forceinline__ uint4 row64(const u16* buf, int tile, int ks) const
+    {
+        return *reinterpret_cast<const uint4*>(at(buf, 32 * kP2 * tile + oa[ks]));
+    }
+    __device__ __forceinline__ uint4 rowN(const u16* buf, int tile, int ks) const
+    {
+        return *reinterpret_cast<const uint4*>(at(buf, 32 * N * tile + 128 * (ks >> 1) + ob[ks & 1]));
+    }
+    __device__ __forceinline__ uint4 tr64(const u16* buf, int m, int off) const   // rows 32 m .. 32 m + 31
+    {
+        const char* a = at(buf, 64 * kP2 * m + off);
+        const uint2 lo = __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4i16*)a));
+        const uint2 hi =
+            __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4i16*)(a + 32 * kP2)));
+        return make_uint4(lo.x, lo.y, hi.x, hi.y);
+    }
 };
 
-// The score tiles (u-tile, t-tile) with u >= t, and those above the diagonal,
-// dealt to the wavefronts: wavefront w evaluates kLowerTile[w] and, for w < 2,
-// kLowerTile[w + 8]; wavefronts 2..7 clear kUpperTile[w - 2].
+// The score tiles (u-tile, t-tile) with u >= t, dealt to the wavefronts:
+// wavefront w evaluates kLowerTile[w] and, for w >= 6, kLowerTile[w + 2]
+// (wavefronts 0 and 1 have the per-token phases).
 __constant__ int2 kLowerTile[10] = {{0, 0}, {1, 0}, {1, 1}, {2, 0}, {2, 1}, {2, 2}, {3, 0}, {3, 1}, {3, 2}, {3, 3}};
-__constant__ int2 kUpperTile[6] = {{0, 1}, {0, 2}, {0, 3}, {1, 2}, {1, 3}, {2, 3}};
 
 // DIRECT: one head slice per group; dB and dC stored by this kernel (bf16).
 template <int N, bool PACKED, bool H32, bool DIRECT>
@@ -408,30 +472,25 @@ template <int N, bool PACKED, bool H32, bool DIRECT>
 // them at every head's start also waited for all the memory operations
 // before them, the previous head's gradient stores included.
 __global__ __launch_bounds__(kT2) void k_bwd2_chunk(BwdParams p, const float* __restrict__ A_logp,
-                                                    const float* __restrict__ Dp)
+                                                       const float* __restrict__ Dp)
 {
-    constexpr int kLdN = ChunkSmem<N>::kLdN;
-    constexpr int kLdF = ChunkSmem<N, H32>::kLdF;
-    constexpr int kLd = ChunkSmem<N, H32>::kLdC;   // (this kernel's 64-wide row stride)
     constexpr int kNT = N / 16;             // n-tiles
     constexpr int kBW = N / 32;             // dB / dC tiles per wavefront
     extern __shared__ __attribute__((aligned(16))) u16 sm2[];
-    u16* Bs = sm2;                      // 64 x kLdN  B   (row t, k = n)
-    u16* BT = Bs + kQ2 * kLdN;          // N x kLd    B^T (row n, k = t)
-    u16* CT = BT + N * kLd;             // N x kLd    C^T (row n, k = u)
-    u16* xs = CT + N * kLd;             // 64 x kLd   x   (row t, k = p)
-    u16* dys = xs + kQ2 * kLd;          // 64 x kLd   dy  (row u, k = p)
-    u16* dyT = dys + kQ2 * kLd;         // 64 x kLd   dy^T (row p, k = u)
-    u16* GsT = dyT + kQ2 * kLd;         // 64 x kLd   Gs^T (row t, k = u)
-    u16* Rs = GsT + kQ2 * kLd;          // 64 x kLd   Rs  (row u, k = t)
-    u16* RsT = Rs + kQ2 * kLd;          // 64 x kLd   Rs^T (row t, k = u)
-    u16* GnS = RsT + kQ2 * kLd;         // 64 x kLdN  Gn  (row p, k = n), from Gn^T
-    float* dyF = reinterpret_cast<float*>(GnS + kQ2 * kLdN);   // H32: 64 x kLdF dy in float32 (row u)
+    u16* const Bs = sm2;
+    u16* const Gn = Bs + kQ2 * N;
+    u16* const xs = Gn + kQ2 * N;
+    u16* const dys = xs + kQ2 * kP2;
+    u16* const Gs = dys + kQ2 * kP2;
+    u16* const Rs = Gs + kQ2 * kP2;
     // per-token factors, double-buffered by head parity (the per-token phase of
     // one head overlaps the next head's set-up)
-    __shared__ float scs2[2][kQ2], sdt2[2][kQ2], seend2[2][kQ2], secs2[2][kQ2];
-    __shared__ float rowp[kQ2][4], colp[kQ2][4], xdxp[kQ2][4], q2p[kQ2][4], dyxp[kQ2][4], q1p[kQ2][kNT];
-    __shared__ float scr[8];
+    __shared__ __attribute__((aligned(16))) float scs2[2][kQ2], sdt2[2][kQ2], seend2[2][kQ2], secs2[2][kQ2];
+    // partial sums of the per-token phase, by token within a slot: of the
+    // scores by row and by column, x . dX~ and x . (Gn B) by p-tile, and
+    // dy . (h_in C) by n-tile; then <Gn, h_in> and dy . x by lane group
+    __shared__ float rowp[4][kQ2], colp[4][kQ2], xdp[2][4][kQ2], q1p[kNT][kQ2];
+    __shared__ float ghp[32], dyxp[32];
 
     const int64_t c = blockIdx.x, b = blockIdx.y;
     const HeadRange hr = head_range(p);
@@ -459,86 +518,127 @@ __global__ __launch_bounds__(kT2) void k_bwd2_chunk(BwdParams p, const float* __
     }
     const int L = L0;
     const int64_t t0 = t00;
-    const u16* Bg = static_cast<const u16*>(p.B);
-    const u16* Cg = static_cast<const u16*>(p.C);
-    const u16* xg = static_cast<const u16*>(p.x);
-    const u16* dyg = static_cast<const u16*>(p.dy);
-    const float* dyg32 = static_cast<const float*>(p.dy);   // H32
-    u16* dxg = static_cast<u16*>(p.dx);
 
-    // B, B^T, C^T of the chunk
+    // B and C of the chunk; cleared: the two score tiles above the diagonal that
+    // the products read, and the partial sums of those that nobody writes
     for (int i = tid; i < kQ2 * N / 8; i += kT2) {
-        const int s = i & 63, n0 = 8 * (i >> 6);   // consecutive lanes: consecutive tokens
+        const int s = i / (N / 8), n0 = 8 * (i % (N / 8));
         uint4 vb = make_uint4(0, 0, 0, 0), vc = vb;
         if (s < L) {
             const int64_t gi = ((t0 + s) * p.G + hr.g) * N + n0;
-            vb = *reinterpret_cast<const uint4*>(Bg + gi);
-            vc = *reinterpret_cast<const uint4*>(Cg + gi);
+            vb = *reinterpret_cast<const uint4*>(static_cast<const u16*>(p.B) + gi);
+            vc = *reinterpret_cast<const uint4*>(static_cast<const u16*>(p.C) + gi);
         }
-        *reinterpret_cast<uint4*>(Bs + s * kLdN + n0) = vb;
-        const uint32_t eb[4] = {vb.x, vb.y, vb.z, vb.w}, ec[4] = {vc.x, vc.y, vc.z, vc.w};
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            BT[(n0 + 2 * e) * kLd + s] = static_cast<u16>(eb[e]);
-            BT[(n0 + 2 * e + 1) * kLd + s] = static_cast<u16>(eb[e] >> 16);
-            CT[(n0 + 2 * e) * kLd + s] = static_cast<u16>(ec[e]);
-            CT[(n0 + 2 * e + 1) * kLd + s] = static_cast<u16>(ec[e] >> 16);
-        }
+        const int m = n0 >> 5, h = (n0 >> 4) & 1, g = (n0 >> 2) & 3;
+        *reinterpret_cast<uint2*>(Bs + perm_off<N>(s, m, h, g)) = make_uint2(vb.x, vb.y);
+        *reinterpret_cast<uint2*>(Bs + perm_off<N>(s, m, h, g + 1)) = make_uint2(vb.z, vb.w);
+        *reinterpret_cast<uint4*>(Gn + tok_off<N>(s, n0)) = vc;
+    }
+    if (w < 4) {   // tiles (u 0, t 1) and (u 2, t 3) of Gs and Rs
+        u16* const dst = w & 1 ? Rs : Gs;
+        const int ut = w & 2;
+        *reinterpret_cast<uint2*>(dst + perm_off<kP2>(16 * (ut + 1) + r, ut >> 1, 0, q)) = make_uint2(0, 0);
+    } else {
+        const int k = w - 4;
+        rowp[k][lane] = 0.f;
+        colp[k][lane] = 0.f;
     }
     __syncthreads();
 
-    // G0 = C B^T on this wavefront's score tiles (C rows straight from global memory)
-    const int ntile = w < 2 ? 2 : 1;
+    // G0 = C B^T on this wavefront's score tiles
+    const int ntile = w >= 6 ? 2 : 1;
     f32x4_t g0[2];
 #pragma unroll
     for (int k = 0; k < 2; ++k) {
         g0[k] = zero4();
         if (k < ntile) {
-            const int2 tl = kLowerTile[w + 8 * k];
-            const int u = 16 * tl.x + r;
-            const int64_t crow = ((t0 + (u < L ? u : 0)) * p.G + hr.g) * N;
+            const int2 tl = kLowerTile[w + 2 * k];
 #pragma unroll
             for (int ks = 0; ks < N / 32; ++ks) {
-                uint4 a = *reinterpret_cast<const uint4*>(Cg + crow + ks * 32 + 8 * q);
-                if (u >= L) a = make_uint4(0, 0, 0, 0);
-                g0[k] = mma(a, ldfrag(Bs, kLdN, 16 * tl.y + r, ks, lane), g0[k]);
+                const uint2 lo = *reinterpret_cast<const uint2*>(Gn + tok_off<N>(16 * tl.x + r, 32 * ks + 4 * q));
+                const uint2 hi = *reinterpret_cast<const uint2*>(Gn + tok_off<N>(16 * tl.x + r, 32 * ks + 16 + 4 * q));
+                g0[k] = mma(make_uint4(lo.x, lo.y, hi.x, hi.y), row_frag<N>(Bs, 16 * tl.y + r, ks, lane), g0[k]);
             }
         }
     }
+    const int pw = w & 3;   // p-tile of dX^T
+    // What every head's dB^T and dC^T products take of B and C, in registers: this
+    // wavefront's n-tile of C^T and B^T, and C where the lane's dC^T tiles lie.
+    // Tile j of the wavefront is n-tile nt, token tile tile_of(j).
+    const int nt = (w * kBW) >> 2;
+    const auto tile_of = [&](int j) { return kBW == 4 ? j : (w & 1) + 2 * j; };
+    uint4 ctf[2], btf[2];
+    uint2 cv[kBW];
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) {
+        ctf[ks] = tr_frag<N>(Gn, ks, 16 * nt, lane);
+        btf[ks] = tr_frag_perm<N>(Bs, ks, nt, lane);
+    }
+#pragma unroll
+    for (int j = 0; j < kBW; ++j)
+        cv[j] = *reinterpret_cast<const uint2*>(Gn + tok_off<N>(16 * tile_of(j) + r, 16 * nt + 4 * q));
 
     f32x4_t dBacc[kBW], dCacc[kBW];
 #pragma unroll
     for (int j = 0; j < kBW; ++j) dBacc[j] = dCacc[j] = zero4();
 
-    // one head's inputs, fetched a head ahead: dt (wavefront 0, lane = token)
-    // and one 8-wide piece of x and of dy per thread (token s_me = lane)
-    const int s_me = lane, p0_me = 8 * w;   // token = lane, 8 p values per wavefront
-    uint32_t pdt = 0;   // raw bits (see load_dt_raw)
+    // one head's inputs, fetched a head ahead: dt (wavefront 0, lane = token) and
+    // a 16-byte piece of x and of dy per thread; rows past a partial chunk read as
+    // zeros through the buffer bounds
+    constexpr int kDtBytes = H32 ? 4 : 2, kDyBytes = H32 ? 4 : 2;
+    const int xrow = static_cast<int>(p.H) * kP2;   // elements between tokens of x and dy
+    uint32_t pdt = 0;   // raw bits, widened where used
     uint4 px = make_uint4(0, 0, 0, 0), pd = px;
     float4 pf0 = make_float4(0.f, 0.f, 0.f, 0.f), pf1 = pf0;   // H32: dy in float32
     const auto fetch = [&](int64_t h) {
-        if (w == 0) pdt = lane < L ? load_dt_raw<H32>(p.dt, (t0 + lane) * p.H + h) : 0u;
-        px = pd = make_uint4(0, 0, 0, 0);
-        pf0 = pf1 = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (s_me < L) {
-            const int64_t gi = ((t0 + s_me) * p.H + h) * kP2 + p0_me;
-            px = *reinterpret_cast<const uint4*>(xg + gi);
-            if constexpr (H32) {
-                pf0 = *reinterpret_cast<const float4*>(dyg32 + gi);
-                pf1 = *reinterpret_cast<const float4*>(dyg32 + gi + 4);
-            } else {
-                pd = *reinterpret_cast<const uint4*>(dyg + gi);
-            }
+        if (w == 0) {
+            const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+                const_cast<char*>(static_cast<const char*>(p.dt)) + (t0 * p.H + h) * kDtBytes, 0,
+                static_cast<int>(((L - 1) * p.H + 1) * kDtBytes), 0x00020000);
+            const int off = lane * static_cast<int>(p.H) * kDtBytes;
+            if constexpr (H32)
+                pdt = __builtin_amdgcn_raw_buffer_load_b32(rs, off, 0, 0);
+            else
+                pdt = __builtin_amdgcn_raw_buffer_load_b16(rs, off, 0, 0);
+        }
+        const int64_t base = (t0 * p.H + h) * kP2;
+        const int off = (tid >> 3) * xrow + 8 * (tid & 7), last = (L - 1) * xrow + kP2;
+        const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc(
+            const_cast<u16*>(static_cast<const u16*>(p.x)) + base, 0, last * static_cast<int>(sizeof(u16)), 0x00020000);
+        const __amdgpu_buffer_rsrc_t rd = __builtin_amdgcn_make_buffer_rsrc(
+            const_cast<char*>(static_cast<const char*>(p.dy)) + base * kDyBytes, 0, last * kDyBytes, 0x00020000);
+        px = __builtin_bit_cast(
+            uint4, __builtin_amdgcn_raw_buffer_load_b128(rx, off * static_cast<int>(sizeof(u16)), 0, 0));
+        if constexpr (H32) {
+            pf0 = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(rd, off * kDyBytes, 0, 0));
+            pf1 = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(rd, off * kDyBytes + 16, 0, 0));
+        } else {
+            pd = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rd, off * kDyBytes, 0, 0));
         }
     };
+    const int staged = tok_off<kP2>(tid >> 3, 8 * (tid & 7));   // a thread's piece of a 64-wide buffer
+    // and Gn^T (pieces for the shared copy) and this wavefront's fragments of
+    // h_in^T, each fetched for the next head once this head's have been used
+    u32x4_t gpc[N / 64];
+    uint4 hinf[2];
+    const auto state_at = [&](int64_t h) { return ((b * p.nC + c) * p.H + h) * kP2 * N; };
+    const auto fetch_gn = [&](int64_t h) {
+        const u16* g = reinterpret_cast<const u16*>(p.gnT) + state_at(h);
+#pragma unroll
+        for (int k = 0; k < N / 64; ++k) gpc[k] = reinterpret_cast<const u32x4_t*>(g)[tid + kT2 * k];
+    };
+    const auto fetch_hin = [&](int64_t h) {
+        const u16* g = reinterpret_cast<const u16*>(p.hin) + state_at(h);
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks) hinf[ks] = *reinterpret_cast<const uint4*>(g + (16 * nt + r) * kP2 + ks * 32 + 8 * q);
+    };
     fetch(hr.lo);
+    fetch_gn(hr.lo);
+    fetch_hin(hr.lo);
 
     for (int64_t h = hr.lo; h < hr.hi; ++h) {
         const int64_t bh = b * p.H + h;
-        const int64_t sbase = ((b * p.nC + c) * p.H + h) * kP2 * N;
-        const u16* GnT = reinterpret_cast<const u16*>(p.gnT) + sbase;   // n x p
-        const u16* HinT = reinterpret_cast<const u16*>(p.hin) + sbase;  // n x p
-        const float Ah = -expf(A_logp[h]);
+        const int64_t hn = h + 1 < hr.hi ? h + 1 : h;   // (branch-free: the last head is fetched again, unused)
         const float Dh = Dp ? Dp[h] : 0.f;
         const int hb = static_cast<int>((h - hr.lo) & 1);
         float* const scs = scs2[hb];
@@ -546,217 +646,195 @@ __global__ __launch_bounds__(kT2) void k_bwd2_chunk(BwdParams p, const float* __
         float* const seend = seend2[hb];
         float* const secs = secs2[hb];
 
-        // this wavefront's state fragments (issued first: they come from HBM)
-        const int pw = w >> 1;                       // p-tile of dX^T
-        uint4 gpc[N / 64], gntf[2], hinf[2];   // pieces of Gn^T for GnS; operand fragments
-#pragma unroll
-        for (int k = 0; k < N / 64; ++k) {
-            // piece (row n = pc % N, p = 8 (pc / N) ..): consecutive lanes, consecutive rows
-            const int pc = tid + kT2 * k, nn = pc % N, p0 = 8 * (pc / N);
-            gpc[k] = reinterpret_cast<const uint4*>(GnT)[nn * (kP2 / 8) + p0 / 8];
-        }
-        {
-            const int nt = (w * kBW) >> 2;   // this wavefront's n-tile of dB^T / dC^T (one per wavefront)
-#pragma unroll
-            for (int ks = 0; ks < 2; ++ks) {
-                gntf[ks] = ldfrag_g(GnT, kP2, 16 * nt + r, ks, lane);
-                hinf[ks] = ldfrag_g(HinT, kP2, 16 * nt + r, ks, lane);
-            }
-        }
         // this head's x, dy (fetched during the previous head) into shared memory
-        if constexpr (H32) {   // the operand copies in bf16, dy also kept in float32
+        if constexpr (H32)
             pd = make_uint4(pack2(pf0.x, pf0.y), pack2(pf0.z, pf0.w), pack2(pf1.x, pf1.y), pack2(pf1.z, pf1.w));
-            *reinterpret_cast<float4*>(dyF + s_me * kLdF + p0_me) = pf0;
-            *reinterpret_cast<float4*>(dyF + s_me * kLdF + p0_me + 4) = pf1;
-        }
-        *reinterpret_cast<uint4*>(xs + s_me * kLd + p0_me) = px;
-        *reinterpret_cast<uint4*>(dys + s_me * kLd + p0_me) = pd;
-        {
-            const uint32_t ed[4] = {pd.x, pd.y, pd.z, pd.w};
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                dyT[(p0_me + 2 * e) * kLd + s_me] = static_cast<u16>(ed[e]);
-                dyT[(p0_me + 2 * e + 1) * kLd + s_me] = static_cast<u16>(ed[e] >> 16);
-            }
-        }
+        *reinterpret_cast<uint4*>(xs + staged) = px;
+        *reinterpret_cast<uint4*>(dys + staged) = pd;
         if (w == 0) {
             // cumsum of dt*A (log2 units) and the per-token factors
-            const float A2 = Ah * kLog2e;
+            const float A2 = -expf(A_logp[h]) * kLog2e;
             const float dtv = dt_of_raw<H32>(pdt);
             const float cs = wave_scan(dtv * A2);
             const float csend = lane_value(cs, L - 1);
             scs[lane] = cs;
             sdt[lane] = dtv;
-            seend[lane] = lane < L ? exp2f(csend - cs) : 0.f;
-            secs[lane] = lane < L ? exp2f(cs) : 0.f;
+            seend[lane] = lane < L ? __builtin_amdgcn_exp2f(csend - cs) : 0.f;
+            secs[lane] = lane < L ? __builtin_amdgcn_exp2f(cs) : 0.f;
         }
-        if (h + 1 < hr.hi) fetch(h + 1);
+        fetch(hn);
         __syncthreads();   // (1) per-head inputs in place
 
+        {
+        const LaneOffs<N> o(lane, pw);
+        const int r = o.r, q = o.q;
         // --- score tiles: R0 = dy x^T (then dt_t), Gs, Rs, l and their sums
 #pragma unroll
         for (int k = 0; k < 2; ++k) {
             if (k < ntile) {
-                const int2 tl = kLowerTile[w + 8 * k];
+                const int2 tl = kLowerTile[w + 2 * k];
                 f32x4_t acc = zero4();
 #pragma unroll
                 for (int ks = 0; ks < 2; ++ks)
-                    acc = mma(ldfrag(dys, kLd, 16 * tl.x + r, ks, lane), ldfrag(xs, kLd, 16 * tl.y + r, ks, lane),
-                              acc);
-                const int t = 16 * tl.y + r;
+                    acc = mma(o.row64(dys, tl.x, ks), o.row64(xs, tl.y, ks), acc);
+                const int t = 16 * tl.y + r, u0 = 16 * tl.x + 4 * q;
                 const float dtt = sdt[t], cst = scs[t];
-                float gs[4], rs[4], colsum = 0.f;
+                const float4 csu = *reinterpret_cast<const float4*>(scs + u0);
+                const float cu[4] = {csu.x, csu.y, csu.z, csu.w};
+                float gs[4], rs[4], l[4];
 #pragma unroll
                 for (int v = 0; v < 4; ++v) {
-                    const int u = 16 * tl.x + 4 * q + v;
-                    float gv = 0.f, rv = 0.f, lv = 0.f;
-                    if (u >= t && u < L) {
-                        const float e = exp2f(scs[u] - cst);
-                        const float r0 = acc[v] * dtt;
-                        gv = e * g0[k][v];
-                        rv = e * r0;
-                        lv = gv * r0;
-                    }
-                    gs[v] = gv;
-                    rs[v] = rv;
-                    colsum += lv;
-                    // row sum of l over the tile's 16 columns t
-                    const float rsum = row_sum16(lv);
-                    if (r == 0) rowp[16 * tl.x + 4 * q + v][tl.y] = rsum;
+                    const bool on = u0 + v >= t && u0 + v < L;
+                    const float e = on ? __builtin_amdgcn_exp2f(cu[v] - cst) : 0.f;
+                    const float r0 = acc[v] * dtt;
+                    gs[v] = e * g0[k][v];
+                    rs[v] = on ? e * r0 : 0.f;
+                    l[v] = on ? gs[v] * r0 : 0.f;
                 }
-                colsum = col_sum4(colsum);
-                if (q == 0) colp[t][tl.x] = colsum;
-                const int u0 = 16 * tl.x + 4 * q;
-                *reinterpret_cast<uint2*>(GsT + t * kLd + u0) = make_uint2(pack2(gs[0], gs[1]), pack2(gs[2], gs[3]));
-                *reinterpret_cast<uint2*>(RsT + t * kLd + u0) = make_uint2(pack2(rs[0], rs[1]), pack2(rs[2], rs[3]));
-#pragma unroll
-                for (int v = 0; v < 4; ++v) Rs[(u0 + v) * kLd + t] = static_cast<u16>(bf16_bits(rs[v]));
+                const float rsum = row_sum16x4(l[0], l[1], l[2], l[3], r);
+                if (r < 4) rowp[tl.y][u0 + r] = rsum;
+                const float csum = col_sum4((l[0] + l[1]) + (l[2] + l[3]));
+                if (q == 0) colp[tl.x][t] = csum;
+                const int off = (tl.x >> 1 ? o.oa[1] : o.oa[0]) + 8 * (tl.x & 1) + 32 * kP2 * tl.y;
+                *reinterpret_cast<uint2*>(reinterpret_cast<char*>(Gs) + off) = make_uint2(pack2(gs[0], gs[1]), pack2(gs[2], gs[3]));
+                *reinterpret_cast<uint2*>(reinterpret_cast<char*>(Rs) + off) = make_uint2(pack2(rs[0], rs[1]), pack2(rs[2], rs[3]));
             }
         }
-        if (w >= 2) {
-            const int2 tl = kUpperTile[w - 2];
-            const int t = 16 * tl.y + r, u0 = 16 * tl.x + 4 * q;
-            *reinterpret_cast<uint2*>(GsT + t * kLd + u0) = make_uint2(0, 0);
-            *reinterpret_cast<uint2*>(RsT + t * kLd + u0) = make_uint2(0, 0);
-#pragma unroll
-            for (int v = 0; v < 4; ++v) Rs[(u0 + v) * kLd + t] = 0;
-            if (r == 0)
-#pragma unroll
-                for (int v = 0; v < 4; ++v) rowp[u0 + v][tl.y] = 0.f;
-            if (q == 0) colp[t][tl.x] = 0.f;
-        }
-        // Gn (p x n) into shared memory from the pieces of Gn^T
 #pragma unroll
         for (int k = 0; k < N / 64; ++k) {
-            const int pc = tid + kT2 * k, nn = pc % N, p0 = 8 * (pc / N);
-            const uint32_t eg[4] = {gpc[k].x, gpc[k].y, gpc[k].z, gpc[k].w};
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                GnS[(p0 + 2 * e) * kLdN + nn] = static_cast<u16>(eg[e]);
-                GnS[(p0 + 2 * e + 1) * kLdN + nn] = static_cast<u16>(eg[e] >> 16);
-            }
+            *reinterpret_cast<u32x4_t*>(Gn + kQ2 * kP2 * k + staged) = gpc[k];
         }
+        }
+        fetch_gn(hn);
         __syncthreads();   // (2) score tiles, their sums and Gn in place
 
-        // --- dX~^T (p x t): dy^T Gs + e(end,t) Gn B^T; dx, and per-token sums
+        // --- dX~^T (p x t): dy^T Gs + e(end,t) Gn B^T; dx, and per-token sums.  P-tile
+        // w % 4, token tiles w / 4 and w / 4 + 2 (whose scores with u < 32 are zero)
+        float sxd[2], sxg[2], sdx = 0.f;
+        const LaneOffs<N> o(lane, pw);
+        const int r = o.r, q = o.q, p0 = 16 * pw + 4 * q;
+        {
+            float4 d32[2];
+            if constexpr (H32) {   // (just read by the fetch: from L2)
+                const __amdgpu_buffer_rsrc_t rd = __builtin_amdgcn_make_buffer_rsrc(
+                    const_cast<float*>(static_cast<const float*>(p.dy)) + (t0 * p.H + h) * kP2, 0,
+                    ((L - 1) * xrow + kP2) * 4, 0x00020000);
 #pragma unroll
-        for (int j = 0; j < 2; ++j) {
-            const int tt = 2 * (w & 1) + j;
-            f32x4_t ai = zero4(), ag = zero4();
-#pragma unroll
-            for (int ks = 0; ks < 2; ++ks)
-                ai = mma(ldfrag(dyT, kLd, 16 * pw + r, ks, lane), ldfrag(GsT, kLd, 16 * tt + r, ks, lane), ai);
-#pragma unroll
-            for (int ks = 0; ks < N / 32; ++ks)
-                ag = mma(ldfrag(GnS, kLdN, 16 * pw + r, ks, lane), ldfrag(Bs, kLdN, 16 * tt + r, ks, lane), ag);
-            const int t = 16 * tt + r, p0 = 16 * pw + 4 * q;
-            const float ee = seend[t], dtt = sdt[t];
-            const uint2 xv = *reinterpret_cast<const uint2*>(xs + t * kLd + p0);
-            const float xf[4] = {lo_f(xv.x), hi_f(xv.x), lo_f(xv.y), hi_f(xv.y)};
-            float df[4];
-            if constexpr (H32) {
-                const float4 d4 = *reinterpret_cast<const float4*>(dyF + t * kLdF + p0);
-                df[0] = d4.x; df[1] = d4.y; df[2] = d4.z; df[3] = d4.w;
-            } else {
-                const uint2 dv = *reinterpret_cast<const uint2*>(dys + t * kLd + p0);
-                df[0] = lo_f(dv.x); df[1] = hi_f(dv.x); df[2] = lo_f(dv.y); df[3] = hi_f(dv.y);
+                for (int j = 0; j < 2; ++j)
+                    d32[j] = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(
+                                                            rd, ((16 * ((w >> 2) + 2 * j) + r) * xrow + p0) * 4, 0, 0));
             }
-            float dx[4], sxd = 0.f, sxg = 0.f, sdx = 0.f;
+            // (rows past a partial chunk are dropped by the buffer bounds: no branch)
+            const __amdgpu_buffer_rsrc_t rdx = __builtin_amdgcn_make_buffer_rsrc(
+                static_cast<u16*>(p.dx) + (t0 * p.H + h) * kP2, 0,
+                ((L - 1) * xrow + kP2) * static_cast<int>(sizeof(u16)), 0x00020000);
+            f32x4_t ai[2], ag[2];
 #pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const float dX = fmaf(ee, ag[v], ai[v]);
-                dx[v] = fmaf(dtt, dX, Dh * df[v]);
-                sxd = fmaf(xf[v], dX, sxd);
-                sxg = fmaf(xf[v], ag[v], sxg);
-                sdx = fmaf(df[v], xf[v], sdx);
-            }
-            if (t < L)
-                *reinterpret_cast<uint2*>(dxg + (t0 + t) * p.H * kP2 + h * kP2 + p0) =
-                    make_uint2(pack2(dx[0], dx[1]), pack2(dx[2], dx[3]));
-            sxd = col_sum4(sxd);
-            sxg = col_sum4(sxg);
-            sdx = col_sum4(sdx);
-            if (q == 0) {
-                xdxp[t][pw] = sxd;
-                q2p[t][pw] = sxg;
-                dyxp[t][pw] = sdx;
-            }
-        }
-
-        // --- dB^T (n x t) += C^T Rs + e(end,t) dt_t Gn^T x^T
-#pragma unroll
-        for (int j = 0; j < kBW; ++j) {
-            const int idx = w * kBW + j, nt = idx >> 2, tt = idx & 3;
-            f32x4_t bi = zero4(), bx = zero4();
+            for (int j = 0; j < 2; ++j) ai[j] = ag[j] = zero4();
 #pragma unroll
             for (int ks = 0; ks < 2; ++ks) {
-                bi = mma(ldfrag(CT, kLd, 16 * nt + r, ks, lane), ldfrag(RsT, kLd, 16 * tt + r, ks, lane), bi);
-                bx = mma(gntf[ks], ldfrag(xs, kLd, 16 * tt + r, ks, lane), bx);
-            }
-            const int t = 16 * tt + r;
-            const float fb = seend[t] * sdt[t];
+                const uint4 a = o.tr64(dys, ks, o.ot);
 #pragma unroll
-            for (int v = 0; v < 4; ++v) dBacc[j][v] += fmaf(fb, bx[v], bi[v]);
+                for (int j = 0; j < 2; ++j)
+                    if (j == 0 || ks == 1) ai[j] = mma(a, o.row64(Gs, (w >> 2) + 2 * j, ks), ai[j]);
+            }
+#pragma unroll
+            for (int ks = 0; ks < N / 32; ++ks) {
+                const uint4 a = o.tr64(Gn, ks, o.ot);
+#pragma unroll
+                for (int j = 0; j < 2; ++j) ag[j] = mma(a, o.rowN(Bs, (w >> 2) + 2 * j, ks), ag[j]);
+            }
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                const int t = 16 * ((w >> 2) + 2 * j) + r;
+                const float ee = seend[t], dtt = sdt[t];
+                const uint2 xv = *reinterpret_cast<const uint2*>(o.at(xs, 32 * kP2 * ((w >> 2) + 2 * j) + o.ox));
+                const float xf[4] = {lo_f(xv.x), hi_f(xv.x), lo_f(xv.y), hi_f(xv.y)};
+                float df[4];
+                if constexpr (H32) {
+                    df[0] = d32[j].x; df[1] = d32[j].y; df[2] = d32[j].z; df[3] = d32[j].w;
+                } else {
+                    const uint2 dv = *reinterpret_cast<const uint2*>(o.at(dys, 32 * kP2 * ((w >> 2) + 2 * j) + o.ox));
+                    df[0] = lo_f(dv.x); df[1] = hi_f(dv.x); df[2] = lo_f(dv.y); df[3] = hi_f(dv.y);
+                }
+                float dx[4];
+                sxd[j] = sxg[j] = 0.f;
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    const float dX = fmaf(ee, ag[j][v], ai[j][v]);
+                    dx[v] = fmaf(dtt, dX, Dh * df[v]);
+                    sxd[j] = fmaf(xf[v], dX, sxd[j]);
+                    sxg[j] = fmaf(xf[v], ag[j][v], sxg[j]);
+                    sdx = fmaf(df[v], xf[v], sdx);
+                }
+                __builtin_amdgcn_raw_buffer_store_b64(u32x2_t{pack2(dx[0], dx[1]), pack2(dx[2], dx[3])}, rdx,
+                                                      (t * xrow + p0) * static_cast<int>(sizeof(u16)), 0, 0);
+            }
+        }
+        // (lane group q: x . dX~ and x . (Gn B) of the first and the second token tile)
+        xdp[q >> 1][pw][16 * ((w >> 2) + 2 * (q & 1)) + r] = col_sum4x4(sxd[0], sxd[1], sxg[0], sxg[1]);
+        sdx = row_sum16(sdx);
+        if (r == 0) dyxp[4 * w + q] = sdx;
+
+        __builtin_amdgcn_sched_barrier(0);
+        // --- dB^T (n x t) += C^T Rs + e(end,t) dt_t Gn^T x^T
+        uint4 gntf[2];
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks) gntf[ks] = o.row64(Gn, nt, ks);
+#pragma unroll
+        for (int j = 0; j < kBW; ++j) {
+            __builtin_amdgcn_sched_barrier(0);
+            const int tt = tile_of(j);
+            f32x4_t bx = zero4();
+#pragma unroll
+            for (int ks = 0; ks < 2; ++ks) {
+                if (j < kBW / 2 || ks == 1)   // (token tiles 2 and 3: no u < 32)
+                    dBacc[j] = mma(ctf[ks], o.row64(Rs, tt, ks), dBacc[j]);
+                bx = mma(gntf[ks], o.row64(xs, tt, ks), bx);
+            }
+            const float fb = seend[16 * tt + r] * sdt[16 * tt + r];
+#pragma unroll
+            for (int v = 0; v < 4; ++v) dBacc[j][v] = fmaf(fb, bx[v], dBacc[j][v]);
         }
         // --- dC^T (n x u) += B^T Rs^T + exp(cs_u) h_in^T dy^T, and dy_u . (h_in C_u)
+        float q1[kBW];
 #pragma unroll
         for (int j = 0; j < kBW; ++j) {
-            const int idx = w * kBW + j, nt = idx >> 2, tt = idx & 3;
-            f32x4_t ci = zero4(), ch = zero4();
+            __builtin_amdgcn_sched_barrier(0);
+            const int tt = tile_of(j);
+            f32x4_t ch = zero4();
 #pragma unroll
             for (int ks = 0; ks < 2; ++ks) {
-                ci = mma(ldfrag(BT, kLd, 16 * nt + r, ks, lane), ldfrag(Rs, kLd, 16 * tt + r, ks, lane), ci);
-                ch = mma(hinf[ks], ldfrag(dys, kLd, 16 * tt + r, ks, lane), ch);
+                if (j >= kBW / 2 || ks == 0)   // (token tiles 0 and 1: no t >= 32)
+                    dCacc[j] = mma(btf[ks], o.tr64(Rs, ks, o.op[kBW == 4 ? j >> 1 : j] + 8 * (tt & 1)), dCacc[j]);
+                ch = mma(hinf[ks], o.row64(dys, tt, ks), ch);
             }
-            const int t = 16 * tt + r;
-            const float fc = secs[t];
-            float q1 = 0.f;
+            const float fc = secs[16 * tt + r];
+            asm volatile("" : "+v"(cv[j].x), "+v"(cv[j].y));   // (kept packed across the heads)
+            const float cf[4] = {lo_f(cv[j].x), hi_f(cv[j].x), lo_f(cv[j].y), hi_f(cv[j].y)};
+            q1[j] = 0.f;
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
-                dCacc[j][v] += fmaf(fc, ch[v], ci[v]);
-                q1 = fmaf(bf(CT[(16 * nt + 4 * q + v) * kLd + t]), ch[v], q1);
+                dCacc[j][v] = fmaf(fc, ch[v], dCacc[j][v]);
+                q1[j] = fmaf(cf[v], ch[v], q1[j]);
             }
-            q1 = col_sum4(q1);
-            if (q == 0) q1p[t][nt] = q1;
         }
-
+        {   // lane group q gets the sum of token tile tile_of(q)
+            const float s = col_sum4x4(q1[0], q1[1], q1[kBW - 2], q1[kBW - 1]);
+            if (q < kBW) q1p[nt][16 * tile_of(q) + r] = s;
+        }
         {
-            // <Gn, h_in> from this wavefront's fragments of Gn^T and h_in^T (one
-            // n-tile; with dstate 64 two wavefronts hold each tile, the even one counts it)
-            float gh = 0.f;
-            if (kBW == 4 || (w & 1) == 0) {
+            // <Gn, h_in>: the diagonal of Gn^T (h_in^T)^T over this wavefront's n-tile
+            // (with dstate 64 two wavefronts hold each tile, the even one counts it)
+            f32x4_t d = zero4();
 #pragma unroll
-                for (int ks = 0; ks < 2; ++ks) {
-                    const uint32_t ea[4] = {gntf[ks].x, gntf[ks].y, gntf[ks].z, gntf[ks].w};
-                    const uint32_t ez[4] = {hinf[ks].x, hinf[ks].y, hinf[ks].z, hinf[ks].w};
-#pragma unroll
-                    for (int e = 0; e < 4; ++e)
-                        gh = fmaf(lo_f(ea[e]), lo_f(ez[e]), fmaf(hi_f(ea[e]), hi_f(ez[e]), gh));
-                }
-            }
-            gh = wave_sum(gh);
-            if (lane == 0) scr[w] = gh;
+            for (int ks = 0; ks < 2; ++ks) d = mma(gntf[ks], hinf[ks], d);
+            float gh = (r & 2) ? ((r & 1) ? d[3] : d[2]) : ((r & 1) ? d[1] : d[0]);
+            gh = r >> 2 == q && (kBW == 4 || (w & 1) == 0) ? gh : 0.f;
+            gh = row_sum16(gh);
+            if (r == 0) ghp[4 * w + q] = gh;
         }
+        fetch_hin(hn);
         __syncthreads();   // (3) per-token partial sums in place
 
         // --- per token (wavefront 1; lane k holds token t = 63 - k, so that a
@@ -768,32 +846,31 @@ __global__ __launch_bounds__(kT2) void k_bwd2_chunk(BwdParams p, const float* __
         if (w == 1) {
             const int t = kQ2 - 1 - lane;
             const bool in = t < L;
-            float s2 = 0.f, row = 0.f, col = 0.f, s1 = 0.f, xd = 0.f, dyx = 0.f;
+            float s2 = 0.f, row = 0.f, col = 0.f, s1 = 0.f, xd = 0.f;
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
-                s2 += q2p[t][k];
-                row += rowp[t][k];
-                col += colp[t][k];
-                xd += xdxp[t][k];
-                dyx += dyxp[t][k];
+                s2 += xdp[1][k][t];
+                row += rowp[k][t];
+                col += colp[k][t];
+                xd += xdp[0][k][t];
             }
 #pragma unroll
-            for (int k = 0; k < kNT; ++k) s1 += q1p[t][k];
+            for (int k = 0; k < kNT; ++k) s1 += q1p[k][t];
             const float q2 = in ? sdt[t] * s2 : 0.f;   // X~_t . (Gn B_t)
-            const float ghs = ((scr[0] + scr[1]) + (scr[2] + scr[3])) + ((scr[4] + scr[5]) + (scr[6] + scr[7]));
+            const float ghs = wave_sum(lane < 32 ? ghp[lane & 31] : 0.f);
             const float hsum = wave_sum(seend[t] * q2);
             float dcs = in ? row - col + secs[t] * s1 - seend[t] * q2 : 0.f;
             if (t == L - 1) dcs += secs[t] * ghs + hsum;   // <Gn, h_out>
             const float da = wave_scan(dcs);   // over tokens t' >= t
             if (in) {
-                const float g = fmaf(Ah, da, xd);
+                const float g = fmaf(-expf(A_logp[h]), da, xd);
                 if constexpr (H32)
                     static_cast<float*>(p.ddt)[(t0 + t) * p.H + h] = g;
                 else
                     static_cast<u16*>(p.ddt)[(t0 + t) * p.H + h] = static_cast<u16>(bf16_bits(g));
             }
             const float sa = wave_sum(in ? sdt[t] * da : 0.f);
-            const float sd = wave_sum(in ? dyx : 0.f);
+            const float sd = wave_sum(lane < 32 ? dyxp[lane & 31] : 0.f);
             if (lane == 0) {
                 p.dAp[bh * p.nC + c] = sa;
                 p.dDp[bh * p.nC + c] = sd;
@@ -807,15 +884,14 @@ __global__ __launch_bounds__(kT2) void k_bwd2_chunk(BwdParams p, const float* __
     // in place, and the launch skips that reduction (bc_direct).
 #pragma unroll
     for (int j = 0; j < kBW; ++j) {
-        const int idx = w * kBW + j, nt = idx >> 2, tt = idx & 3;
-        const int t = 16 * tt + r;
+        const int t = 16 * tile_of(j) + r;
         if (t < L) {
             if constexpr (DIRECT) {
                 const int64_t o = ((t0 + t) * p.G + hr.g) * N + 16 * nt + 4 * q;
                 *reinterpret_cast<uint2*>(static_cast<u16*>(p.dB) + o) =
-                    make_uint2(rne_pair(dBacc[j][0], dBacc[j][1]), rne_pair(dBacc[j][2], dBacc[j][3]));
+                    make_uint2(pack2(dBacc[j][0], dBacc[j][1]), pack2(dBacc[j][2], dBacc[j][3]));
                 *reinterpret_cast<uint2*>(static_cast<u16*>(p.dC) + o) =
-                    make_uint2(rne_pair(dCacc[j][0], dCacc[j][1]), rne_pair(dCacc[j][2], dCacc[j][3]));
+                    make_uint2(pack2(dCacc[j][0], dCacc[j][1]), pack2(dCacc[j][2], dCacc[j][3]));
             } else {
                 const int64_t o = ((hr.slice * p.b * p.T + t0 + t) * p.G + hr.g) * N + 16 * nt + 4 * q;
                 *reinterpret_cast<float4*>(p.dBp + o) =
@@ -844,7 +920,7 @@ hipError_t launch_fast(const BwdParams& params, hipStream_t st, hipEvent_t ev0, 
     p.bc_direct = p.S == 1 && reinterpret_cast<uintptr_t>(p.dB) % 8 == 0 && reinterpret_cast<uintptr_t>(p.dC) % 8 == 0;
     const bool packed = p.vtab != nullptr, h32 = p.h32 != 0, direct = p.bc_direct != 0;
     if (packed && h32) return hipErrorInvalidValue;   // float32 handoffs: plain rows only
-    const size_t sm_chunk = h32 ? ChunkSmem<N, true>::kBytes : ChunkSmem<N>::kBytes;
+    const size_t sm_chunk = chunk_smem<N>();
     hipError_t e;
     if (packed)   // one workgroup per (sequence, head) and direction
         hipLaunchKernelGGL((k_bwd2_pass<N, true, false>), dim3(static_cast<unsigned>(p.nseq * p.H), 2), dim3(kPassT),
