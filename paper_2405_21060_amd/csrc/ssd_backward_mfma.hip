@@ -354,12 +354,13 @@ __global__ __launch_bounds__(kPassT, H32 ? 2 : 1) void k_bwd2_pass(BwdParams p)
 // software rounding, products over the zero half of the scores, and state loads
 // issued at the head that uses them took 564 us at the 2.7B shape (4 x 4,096
 // tokens, 80 heads); reading one copy transposed 467, with the states fetched a
-// head ahead 403.  (128 registers, two workgroups per compute unit: 1,455 us,
-// the operands fetched ahead are spilled.)
+// head ahead 403, and as a pipeline over the heads with one barrier a head
+// instead of three 364.  (128 registers, two workgroups per compute unit: 1,455
+// us, the operands fetched ahead are spilled.)
 template <int N>
 constexpr size_t chunk_smem()
 {
-    return sizeof(u16) * (2 * static_cast<size_t>(kQ2) * N + 4 * kQ2 * kP2);
+    return sizeof(u16) * (3 * static_cast<size_t>(kQ2) * N + (3 * 2 + 2 * 2) * kQ2 * kP2);
 }
 
 // Element offset of column 32 m + 16 h + 4 g (+ 0..3) of row s in a buffer whose
@@ -478,19 +479,20 @@ __global__ __launch_bounds__(kT2) void k_bwd2_chunk(BwdParams p, const float* __
     constexpr int kBW = N / 32;             // dB / dC tiles per wavefront
     extern __shared__ __attribute__((aligned(16))) u16 sm2[];
     u16* const Bs = sm2;
-    u16* const Gn = Bs + kQ2 * N;
-    u16* const xs = Gn + kQ2 * N;
-    u16* const dys = xs + kQ2 * kP2;
-    u16* const Gs = dys + kQ2 * kP2;
-    u16* const Rs = Gs + kQ2 * kP2;
-    // per-token factors, double-buffered by head parity (the per-token phase of
-    // one head overlaps the next head's set-up)
-    __shared__ __attribute__((aligned(16))) float scs2[2][kQ2], sdt2[2][kQ2], seend2[2][kQ2], secs2[2][kQ2];
+    u16* const Gn2 = Bs + kQ2 * N;             // [2]
+    u16* const xs3 = Gn2 + 2 * kQ2 * N;        // [3]
+    u16* const dys3 = xs3 + 3 * kQ2 * kP2;     // [3]
+    u16* const Gs2 = dys3 + 3 * kQ2 * kP2;     // [2]
+    u16* const Rs2 = Gs2 + 2 * kQ2 * kP2;      // [2]
+    // per-token factors, by head (mod 4): written two heads ahead, read last by the
+    // per-token phase a head behind
+    __shared__ __attribute__((aligned(16))) float scs4[4][kQ2], sdt4[4][kQ2], seend4[4][kQ2], secs4[4][kQ2];
     // partial sums of the per-token phase, by token within a slot: of the
-    // scores by row and by column, x . dX~ and x . (Gn B) by p-tile, and
-    // dy . (h_in C) by n-tile; then <Gn, h_in> and dy . x by lane group
-    __shared__ float rowp[4][kQ2], colp[4][kQ2], xdp[2][4][kQ2], q1p[kNT][kQ2];
-    __shared__ float ghp[32], dyxp[32];
+    // scores by row and by column (by head mod 3), x . dX~ and x . (Gn B) by
+    // p-tile, and dy . (h_in C) by n-tile; then <Gn, h_in> and dy . x by lane
+    // group (by head mod 2)
+    __shared__ float rowp3[3][4][kQ2], colp3[3][4][kQ2], xdp2[2][2][4][kQ2], q1p2[2][kNT][kQ2];
+    __shared__ float ghp2[2][32], dyxp2[2][32];
 
     const int64_t c = blockIdx.x, b = blockIdx.y;
     const HeadRange hr = head_range(p);
@@ -532,16 +534,16 @@ __global__ __launch_bounds__(kT2) void k_bwd2_chunk(BwdParams p, const float* __
         const int m = n0 >> 5, h = (n0 >> 4) & 1, g = (n0 >> 2) & 3;
         *reinterpret_cast<uint2*>(Bs + perm_off<N>(s, m, h, g)) = make_uint2(vb.x, vb.y);
         *reinterpret_cast<uint2*>(Bs + perm_off<N>(s, m, h, g + 1)) = make_uint2(vb.z, vb.w);
-        *reinterpret_cast<uint4*>(Gn + tok_off<N>(s, n0)) = vc;
+        *reinterpret_cast<uint4*>(Gn2 + tok_off<N>(s, n0)) = vc;
     }
     if (w < 4) {   // tiles (u 0, t 1) and (u 2, t 3) of Gs and Rs
-        u16* const dst = w & 1 ? Rs : Gs;
+        u16* const dst = w & 1 ? Rs2 : Gs2;
         const int ut = w & 2;
-        *reinterpret_cast<uint2*>(dst + perm_off<kP2>(16 * (ut + 1) + r, ut >> 1, 0, q)) = make_uint2(0, 0);
+        for (int k = 0; k < 2; ++k)
+            *reinterpret_cast<uint2*>(dst + kQ2 * kP2 * k + perm_off<kP2>(16 * (ut + 1) + r, ut >> 1, 0, q)) =
+                make_uint2(0, 0);
     } else {
-        const int k = w - 4;
-        rowp[k][lane] = 0.f;
-        colp[k][lane] = 0.f;
+        for (int k = 0; k < 3; ++k) rowp3[k][w - 4][lane] = colp3[k][w - 4][lane] = 0.f;
     }
     __syncthreads();
 
@@ -555,8 +557,8 @@ __global__ __launch_bounds__(kT2) void k_bwd2_chunk(BwdParams p, const float* __
             const int2 tl = kLowerTile[w + 2 * k];
 #pragma unroll
             for (int ks = 0; ks < N / 32; ++ks) {
-                const uint2 lo = *reinterpret_cast<const uint2*>(Gn + tok_off<N>(16 * tl.x + r, 32 * ks + 4 * q));
-                const uint2 hi = *reinterpret_cast<const uint2*>(Gn + tok_off<N>(16 * tl.x + r, 32 * ks + 16 + 4 * q));
+                const uint2 lo = *reinterpret_cast<const uint2*>(Gn2 + tok_off<N>(16 * tl.x + r, 32 * ks + 4 * q));
+                const uint2 hi = *reinterpret_cast<const uint2*>(Gn2 + tok_off<N>(16 * tl.x + r, 32 * ks + 16 + 4 * q));
                 g0[k] = mma(make_uint4(lo.x, lo.y, hi.x, hi.y), row_frag<N>(Bs, 16 * tl.y + r, ks, lane), g0[k]);
             }
         }
@@ -571,12 +573,12 @@ __global__ __launch_bounds__(kT2) void k_bwd2_chunk(BwdParams p, const float* __
     uint2 cv[kBW];
 #pragma unroll
     for (int ks = 0; ks < 2; ++ks) {
-        ctf[ks] = tr_frag<N>(Gn, ks, 16 * nt, lane);
+        ctf[ks] = tr_frag<N>(Gn2, ks, 16 * nt, lane);
         btf[ks] = tr_frag_perm<N>(Bs, ks, nt, lane);
     }
 #pragma unroll
     for (int j = 0; j < kBW; ++j)
-        cv[j] = *reinterpret_cast<const uint2*>(Gn + tok_off<N>(16 * tile_of(j) + r, 16 * nt + 4 * q));
+        cv[j] = *reinterpret_cast<const uint2*>(Gn2 + tok_off<N>(16 * tile_of(j) + r, 16 * nt + 4 * q));
 
     f32x4_t dBacc[kBW], dCacc[kBW];
 #pragma unroll
@@ -632,20 +634,22 @@ __global__ __launch_bounds__(kT2) void k_bwd2_chunk(BwdParams p, const float* __
 #pragma unroll
         for (int ks = 0; ks < 2; ++ks) hinf[ks] = *reinterpret_cast<const uint4*>(g + (16 * nt + r) * kP2 + ks * 32 + 8 * q);
     };
-    fetch(hr.lo);
-    fetch_gn(hr.lo);
-    fetch_hin(hr.lo);
-
-    for (int64_t h = hr.lo; h < hr.hi; ++h) {
-        const int64_t bh = b * p.H + h;
-        const int64_t hn = h + 1 < hr.hi ? h + 1 : h;   // (branch-free: the last head is fetched again, unused)
-        const float Dh = Dp ? Dp[h] : 0.f;
-        const int hb = static_cast<int>((h - hr.lo) & 1);
-        float* const scs = scs2[hb];
-        float* const sdt = sdt2[hb];
-        float* const seend = seend2[hb];
-        float* const secs = secs2[hb];
-
+    // The walk over the heads is a pipeline with one barrier a head: while the
+    // products of head h run, its workgroup stages x, dy and the factors of head
+    // h + 2, evaluates the scores of h + 1, and finishes the per-token sums of
+    // h - 1.  Each of these reads what an earlier step wrote and writes buffers
+    // that nobody reads in this step: x, dy and the scores' sums lie in three
+    // buffers (head mod 3), the scores, Gn and the other sums in two, the factors
+    // in four.  Past the last head the early stages run on its inputs once more
+    // (no branches: the compiler then counts the loads in flight); nobody reads
+    // their results.
+    const auto setup = [&](int64_t h, int x3, int k) {   // from the registers of fetch(h)
+        u16* const xs = xs3 + kQ2 * kP2 * x3;
+        u16* const dys = dys3 + kQ2 * kP2 * x3;
+        float* const scs = scs4[k];
+        float* const sdt = sdt4[k];
+        float* const seend = seend4[k];
+        float* const secs = secs4[k];
         // this head's x, dy (fetched during the previous head) into shared memory
         if constexpr (H32)
             pd = make_uint4(pack2(pf0.x, pf0.y), pack2(pf0.z, pf0.w), pack2(pf1.x, pf1.y), pack2(pf1.z, pf1.w));
@@ -662,10 +666,21 @@ __global__ __launch_bounds__(kT2) void k_bwd2_chunk(BwdParams p, const float* __
             seend[lane] = lane < L ? __builtin_amdgcn_exp2f(csend - cs) : 0.f;
             secs[lane] = lane < L ? __builtin_amdgcn_exp2f(cs) : 0.f;
         }
-        fetch(hn);
-        __syncthreads();   // (1) per-head inputs in place
-
-        {
+    };
+    const auto store_gn = [&](int g2) {   // from the registers of fetch_gn
+#pragma unroll
+        for (int k = 0; k < N / 64; ++k)
+            *reinterpret_cast<u32x4_t*>(Gn2 + kQ2 * N * g2 + kQ2 * kP2 * k + staged) = gpc[k];
+    };
+    const auto scores = [&](int x3, int g2, int k4) {
+        const u16* const xs = xs3 + kQ2 * kP2 * x3;
+        const u16* const dys = dys3 + kQ2 * kP2 * x3;
+        u16* const Gs = Gs2 + kQ2 * kP2 * g2;
+        u16* const Rs = Rs2 + kQ2 * kP2 * g2;
+        const float* const scs = scs4[k4];
+        const float* const sdt = sdt4[k4];
+        auto& rowp = rowp3[x3];
+        auto& colp = colp3[x3];
         const LaneOffs<N> o(lane, pw);
         const int r = o.r, q = o.q;
         // --- score tiles: R0 = dy x^T (then dt_t), Gs, Rs, l and their sums
@@ -700,14 +715,87 @@ __global__ __launch_bounds__(kT2) void k_bwd2_chunk(BwdParams p, const float* __
                 *reinterpret_cast<uint2*>(reinterpret_cast<char*>(Rs) + off) = make_uint2(pack2(rs[0], rs[1]), pack2(rs[2], rs[3]));
             }
         }
+    };
+    // wavefront 1; lane k holds token t = 63 - k, so that a prefix sum over lanes
+    // is a suffix sum over tokens: dcs, then the decay gradients
+    const auto per_token = [&](int64_t h, int x3, int g2, int k4) {
+        const float* const sdt = sdt4[k4];
+        const float* const seend = seend4[k4];
+        const float* const secs = secs4[k4];
+        const auto& rowp = rowp3[x3];
+        const auto& colp = colp3[x3];
+        const auto& xdp = xdp2[g2];
+        const auto& q1p = q1p2[g2];
+        const auto& ghp = ghp2[g2];
+        const auto& dyxp = dyxp2[g2];
+        const int64_t bh = b * p.H + h;
+            const int t = kQ2 - 1 - lane;
+            const bool in = t < L;
+            float s2 = 0.f, row = 0.f, col = 0.f, s1 = 0.f, xd = 0.f;
 #pragma unroll
-        for (int k = 0; k < N / 64; ++k) {
-            *reinterpret_cast<u32x4_t*>(Gn + kQ2 * kP2 * k + staged) = gpc[k];
-        }
-        }
-        fetch_gn(hn);
-        __syncthreads();   // (2) score tiles, their sums and Gn in place
+            for (int k = 0; k < 4; ++k) {
+                s2 += xdp[1][k][t];
+                row += rowp[k][t];
+                col += colp[k][t];
+                xd += xdp[0][k][t];
+            }
+#pragma unroll
+            for (int k = 0; k < kNT; ++k) s1 += q1p[k][t];
+            const float q2 = in ? sdt[t] * s2 : 0.f;   // X~_t . (Gn B_t)
+            const float ghs = wave_sum(lane < 32 ? ghp[lane & 31] : 0.f);
+            const float hsum = wave_sum(seend[t] * q2);
+            float dcs = in ? row - col + secs[t] * s1 - seend[t] * q2 : 0.f;
+            if (t == L - 1) dcs += secs[t] * ghs + hsum;   // <Gn, h_out>
+            const float da = wave_scan(dcs);   // over tokens t' >= t
+            if (in) {
+                const float g = fmaf(-expf(A_logp[h]), da, xd);
+                if constexpr (H32)
+                    static_cast<float*>(p.ddt)[(t0 + t) * p.H + h] = g;
+                else
+                    static_cast<u16*>(p.ddt)[(t0 + t) * p.H + h] = static_cast<u16>(bf16_bits(g));
+            }
+            const float sa = wave_sum(in ? sdt[t] * da : 0.f);
+            const float sd = wave_sum(lane < 32 ? dyxp[lane & 31] : 0.f);
+            if (lane == 0) {
+                p.dAp[bh * p.nC + c] = sa;
+                p.dDp[bh * p.nC + c] = sd;
+            }
+    };
+    const auto clamp = [&](int64_t h) { return h < hr.hi ? h : hr.hi - 1; };
+    fetch(hr.lo);
+    fetch_gn(hr.lo);
+    fetch_hin(hr.lo);
+    setup(hr.lo, 0, 0);
+    fetch(clamp(hr.lo + 1));
+    setup(clamp(hr.lo + 1), 1, 1);
+    fetch(clamp(hr.lo + 2));
+    __syncthreads();
+    store_gn(0);   // (over C, which all have read)
+    fetch_gn(clamp(hr.lo + 1));
+    scores(0, 0, 0);
+    __syncthreads();
+    int x0 = 0, x1 = 1, x2 = 2;   // buffers of heads h, h + 1, h + 2 (= h - 1)
+    for (int64_t h = hr.lo; h < hr.hi; ++h) {
+        const int k = static_cast<int>(h - hr.lo), g2 = k & 1, k4 = k & 3;
+        setup(clamp(h + 2), x2, (k + 2) & 3);
+        fetch(clamp(h + 3));
+        store_gn(g2 ^ 1);
+        fetch_gn(clamp(h + 2));
+        scores(x1, g2 ^ 1, (k + 1) & 3);
 
+        const float Dh = Dp ? Dp[h] : 0.f;
+        const u16* const xs = xs3 + kQ2 * kP2 * x0;
+        const u16* const dys = dys3 + kQ2 * kP2 * x0;
+        const u16* const Gs = Gs2 + kQ2 * kP2 * g2;
+        const u16* const Rs = Rs2 + kQ2 * kP2 * g2;
+        const u16* const Gn = Gn2 + kQ2 * N * g2;
+        const float* const sdt = sdt4[k4];
+        const float* const seend = seend4[k4];
+        const float* const secs = secs4[k4];
+        auto& xdp = xdp2[g2];
+        auto& q1p = q1p2[g2];
+        auto& ghp = ghp2[g2];
+        auto& dyxp = dyxp2[g2];
         // --- dX~^T (p x t): dy^T Gs + e(end,t) Gn B^T; dx, and per-token sums.  P-tile
         // w % 4, token tiles w / 4 and w / 4 + 2 (whose scores with u < 32 are zero)
         float sxd[2], sxg[2], sdx = 0.f;
@@ -776,14 +864,12 @@ __global__ __launch_bounds__(kT2) void k_bwd2_chunk(BwdParams p, const float* __
         sdx = row_sum16(sdx);
         if (r == 0) dyxp[4 * w + q] = sdx;
 
-        __builtin_amdgcn_sched_barrier(0);
         // --- dB^T (n x t) += C^T Rs + e(end,t) dt_t Gn^T x^T
         uint4 gntf[2];
 #pragma unroll
         for (int ks = 0; ks < 2; ++ks) gntf[ks] = o.row64(Gn, nt, ks);
 #pragma unroll
         for (int j = 0; j < kBW; ++j) {
-            __builtin_amdgcn_sched_barrier(0);
             const int tt = tile_of(j);
             f32x4_t bx = zero4();
 #pragma unroll
@@ -800,7 +886,6 @@ __global__ __launch_bounds__(kT2) void k_bwd2_chunk(BwdParams p, const float* __
         float q1[kBW];
 #pragma unroll
         for (int j = 0; j < kBW; ++j) {
-            __builtin_amdgcn_sched_barrier(0);
             const int tt = tile_of(j);
             f32x4_t ch = zero4();
 #pragma unroll
@@ -834,48 +919,17 @@ __global__ __launch_bounds__(kT2) void k_bwd2_chunk(BwdParams p, const float* __
             gh = row_sum16(gh);
             if (r == 0) ghp[4 * w + q] = gh;
         }
-        fetch_hin(hn);
-        __syncthreads();   // (3) per-token partial sums in place
-
-        // --- per token (wavefront 1; lane k holds token t = 63 - k, so that a
-        // prefix sum over lanes is a suffix sum over tokens): dcs, then the decay
-        // gradients.  The other wavefronts go on to the next head's set-up
-        // meanwhile; what they write there (inputs, the other buffer of
-        // per-token factors) this does not read, and the partial sums are
-        // rewritten only after the next barrier (1).
-        if (w == 1) {
-            const int t = kQ2 - 1 - lane;
-            const bool in = t < L;
-            float s2 = 0.f, row = 0.f, col = 0.f, s1 = 0.f, xd = 0.f;
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                s2 += xdp[1][k][t];
-                row += rowp[k][t];
-                col += colp[k][t];
-                xd += xdp[0][k][t];
-            }
-#pragma unroll
-            for (int k = 0; k < kNT; ++k) s1 += q1p[k][t];
-            const float q2 = in ? sdt[t] * s2 : 0.f;   // X~_t . (Gn B_t)
-            const float ghs = wave_sum(lane < 32 ? ghp[lane & 31] : 0.f);
-            const float hsum = wave_sum(seend[t] * q2);
-            float dcs = in ? row - col + secs[t] * s1 - seend[t] * q2 : 0.f;
-            if (t == L - 1) dcs += secs[t] * ghs + hsum;   // <Gn, h_out>
-            const float da = wave_scan(dcs);   // over tokens t' >= t
-            if (in) {
-                const float g = fmaf(-expf(A_logp[h]), da, xd);
-                if constexpr (H32)
-                    static_cast<float*>(p.ddt)[(t0 + t) * p.H + h] = g;
-                else
-                    static_cast<u16*>(p.ddt)[(t0 + t) * p.H + h] = static_cast<u16>(bf16_bits(g));
-            }
-            const float sa = wave_sum(in ? sdt[t] * da : 0.f);
-            const float sd = wave_sum(lane < 32 ? dyxp[lane & 31] : 0.f);
-            if (lane == 0) {
-                p.dAp[bh * p.nC + c] = sa;
-                p.dDp[bh * p.nC + c] = sd;
-            }
-        }
+        fetch_hin(clamp(h + 1));
+        if (w == 1 && h > hr.lo) per_token(h - 1, x2, g2 ^ 1, (k + 3) & 3);
+        __syncthreads();
+        const int t = x0;
+        x0 = x1;
+        x1 = x2;
+        x2 = t;
+    }
+    if (w == 1) {
+        const int k = static_cast<int>(hr.hi - 1 - hr.lo);
+        per_token(hr.hi - 1, x2, k & 1, k & 3);
     }
 
     // this slice's dB and dC for the chunk: lane holds n = 16 nt + 4 q + v, t = 16 tt + r.
