@@ -177,7 +177,7 @@ bool fused_shape(const ssd::Shape& s)
 // the general layout (fixed scratch sized for it): what those took stays taken.
 // Elsewhere the fused ones are the faster at every size (2 x 4096 tokens, 40
 // heads of 128, N 128: 115 us against 2705 on the general kernels as they were,
-// about 400 as they are).
+// 607 as they are).
 bool fused_only(const ssd::Shape& s) { return fused_shape(s) && s.P == ssd::kFusedP && s.Q == ssd::kFusedQ; }
 
 size_t general_bytes(const ssd::Shape& s)
