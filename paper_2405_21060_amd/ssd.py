@@ -391,14 +391,39 @@ def decode_step(x, dt, A_log, B, C, state, D=None, out=None):
     """
     import torch
 
+    # One expression over what the checks ask for (this call is shorter on the
+    # device than its checks are here); they say what is wrong when it fails.
+    f32, xt, on = torch.float32, x.dtype, x.get_device()
+    if not (x.is_cuda and (xt is torch.bfloat16 or xt is f32)
+            and A_log is not None and state is not None
+            and dt.dtype is xt and B.dtype is xt and C.dtype is xt and A_log.dtype is f32 and state.dtype is f32
+            and dt.get_device() == on and B.get_device() == on and C.get_device() == on
+            and A_log.get_device() == on and state.get_device() == on
+            and x.is_contiguous() and dt.is_contiguous() and A_log.is_contiguous() and B.is_contiguous()
+            and C.is_contiguous() and state.is_contiguous()
+            and (D is None or (D.dtype is f32 and D.get_device() == on and D.is_contiguous()))):
+        _check_decode(x, dt, A_log, B, C, state, D)
+    b, H, P = x.shape
+    shape = B.shape
+    G, N = shape[1], shape[2]
+    prob = SsdProblem(b, 1, H, P, N, G, 256, 0, SSD_DTYPE_F32 if xt is f32 else SSD_DTYPE_BF16)
+    y = out if out is not None else torch.empty_like(x)
+    rc = load_library().ssd_decode_step(
+        prob, x.data_ptr(), dt.data_ptr(), _ptr(A_log), B.data_ptr(), C.data_ptr(), _ptr(D), _ptr(state), y.data_ptr(),
+        torch._C._cuda_getCurrentRawStream(on))
+    if rc != SSD_OK:
+        raise SsdError(rc, "ssd_decode_step")
+    return y
+
+
+def _check_decode(x, dt, A_log, B, C, state, D):
+    """The checks of ``decode_step``, one by one."""
+    import torch
+
     dev = x.device
     if dev.type != "cuda":
         raise ValueError("tensors must live on a HIP device")
-    if x.dtype == torch.bfloat16:
-        dtype = SSD_DTYPE_BF16
-    elif x.dtype == torch.float32:
-        dtype = SSD_DTYPE_F32
-    else:
+    if x.dtype not in (torch.bfloat16, torch.float32):
         raise TypeError("x must be float32 or bfloat16")
     for name, t in (("dt", dt), ("B", B), ("C", C)):
         if t.dtype != x.dtype:
@@ -409,15 +434,6 @@ def decode_step(x, dt, A_log, B, C, state, D=None, out=None):
     for t in (x, dt, A_log, B, C, D, state):
         if t is not None and (t.device != dev or not t.is_contiguous()):
             raise ValueError("all tensors must be contiguous and on x's device")
-    b, H, P = x.shape
-    G, N = B.shape[1], B.shape[2]
-    prob = make_problem(b, 1, H, P, N, G, 256, dtype, 0)
-    y = out if out is not None else torch.empty_like(x)
-    rc = ssd_decode_step(prob, _ptr(x), _ptr(dt), _ptr(A_log), _ptr(B), _ptr(C), _ptr(D),
-                         _ptr(state), _ptr(y), torch.cuda.current_stream(dev).cuda_stream)
-    if rc != SSD_OK:
-        raise SsdError(rc, "ssd_decode_step")
-    return y
 
 
 def _span_problem(dt, C, P):
