@@ -702,9 +702,9 @@ __global__ __launch_bounds__(kT2) void k_bwd2_chunk(BwdParams p, const float* __
 #pragma unroll
                 for (int v = 0; v < 4; ++v) {
                     const bool on = u0 + v >= t && u0 + v < L;
-                    const float e = on ? __builtin_amdgcn_exp2f(cu[v] - cst) : 0.f;
+                    const float e = __builtin_amdgcn_exp2f(cu[v] - cst);
                     const float r0 = acc[v] * dtt;
-                    gs[v] = e * g0[k][v];
+                    gs[v] = on ? e * g0[k][v] : 0.f;   // (not 0 times what may be infinite)
                     rs[v] = on ? e * r0 : 0.f;
                     l[v] = on ? gs[v] * r0 : 0.f;
                 }

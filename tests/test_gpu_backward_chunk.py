@@ -28,3 +28,25 @@ def test_edges(N, T, heads, per_slice, tune):
     got, ref = gpu_backward(inp, dy, dfinal, True, True), oracle_backward(inp, dy, dfinal, True, True)
     for k in ("dx", "ddt", "dB", "dC", "dA_log", "dD", "dinit"):
         check(k, got[k], ref[k], TOL["bf16"])
+
+
+@pytest.mark.parametrize("N", [64, 128])
+def test_later_tokens_do_not_see_an_infinite_score(N):
+    """C of one token not finite: its scores with later tokens are masked, so dx
+    and ddt of those are what they are with a finite C."""
+    import torch
+    from paper_2405_21060_amd import ssd
+    from tests.ssd_harness import act_to_device, to_device
+
+    announce("backward N %d, one token's C infinite" % N)
+    inp = make_inputs(Problem(1, 50, 2, 64, N, 1, 256, "bf16", init_states=True), 38)
+    dy, dfinal = make_grad_inputs(inp.problem, 38)
+    d, g = to_device(inp), []
+    for bad in (False, True):
+        C = d["C"].clone()
+        if bad:
+            C[0, 18] = float("inf")
+        g.append(ssd.backward(d["x"], d["dt"], d["A_log"], d["B"], C, act_to_device(dy), D=d["D"],
+                              initial_states=d["initial_states"], dfinal_states=torch.from_numpy(dfinal).cuda()))
+    for k in ("dx", "ddt"):
+        assert torch.equal(g[0][k][:, 19:], g[1][k][:, 19:]), k
