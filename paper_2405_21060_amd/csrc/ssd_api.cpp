@@ -158,12 +158,17 @@ bool fused_packed_ok(const ssd_problem* prob)
 
 bool aligned16(const void* p) { return reinterpret_cast<uintptr_t>(p) % 16 == 0; }
 
+// The fused kernels' own shape: headdim 64, chunks of 256.  Its Gram matrix is
+// held in bf16; at their other shapes (headdim 128, shorter chunks) in float32,
+// as the general kernels hold it there.
+bool fused_own(const ssd::Shape& s) { return s.P == ssd::kFusedP && s.Q == ssd::kFusedQ; }
+
 // Layout of the fused kernels for a call: their heads of 64 features and
 // chunks of 256 tokens (nseq > 0: one packed row of nseq sequences).
 ssd::FusedLayout fused_plan(const ssd::Shape& s, int64_t nseq)
 {
     return ssd::fused_layout(s.b, s.T, s.H * (s.P / ssd::kFusedP), s.N, s.G,
-                             (s.T + ssd::kFusedQ - 1) / ssd::kFusedQ, nseq);
+                             (s.T + ssd::kFusedQ - 1) / ssd::kFusedQ, nseq, !fused_own(s));
 }
 
 bool fused_shape(const ssd::Shape& s)
@@ -175,10 +180,9 @@ bool fused_shape(const ssd::Shape& s)
 // Their other shapes (headdim 128, shorter chunks) fall back to the general
 // kernels where an operand is not 16-byte aligned or the workspace holds only
 // the general layout (fixed scratch sized for it): what those took stays taken.
-// Elsewhere the fused ones are the faster at every size (2 x 4096 tokens, 40
-// heads of 128, N 128: 115 us against 2705 on the general kernels as they were,
-// 607 as they are).
-bool fused_only(const ssd::Shape& s) { return fused_shape(s) && s.P == ssd::kFusedP && s.Q == ssd::kFusedQ; }
+// Elsewhere the fused ones are the faster (2 x 4096 tokens, 40 heads of 128,
+// N 128: 128 us against 607 on the general kernels).
+bool fused_only(const ssd::Shape& s) { return fused_shape(s) && fused_own(s); }
 
 size_t general_bytes(const ssd::Shape& s)
 {
@@ -345,6 +349,7 @@ int forward_impl(const ssd_problem* prob, const ssd_block_opts* opts, const void
         f.fin = final_states;
         char* base = static_cast<char*>(workspace);
         f.gram = reinterpret_cast<uint16_t*>(base + fw.gram);
+        if (!fused_own(s)) f.gram_lo = reinterpret_cast<uint16_t*>(base + fw.gram_lo);
         f.BT = reinterpret_cast<uint16_t*>(base + fw.BT);
         f.ring = reinterpret_cast<float*>(base + fw.ring);
         f.flags = reinterpret_cast<int*>(base + fw.flags);

@@ -4,7 +4,9 @@
 // the other), state N in {64, 128, 256} (256: two column blocks of 128), chunks
 // of Q = 256 tokens whatever block length the caller names (the result does not
 // depend on it); plain rows, or one packed row of sequences (Section
-// 8.3) through a chunk table built on the device.
+// 8.3) through a chunk table built on the device.  At P = 64 called with Q = 256
+// the Gram matrix is held in bf16; at the other shapes (G32) in float32, so that
+// a score is rounded once, after its mask, as the general kernels do it there.
 //
 // Two launches per call (a packed row adds the small kernels that build and
 // order its chunk table).
@@ -91,6 +93,28 @@ __device__ __forceinline__ u32 pack_bf16x2(float lo, float hi)
     v[0] = static_cast<__bf16>(lo);
     v[1] = static_cast<__bf16>(hi);
     return __builtin_bit_cast(u32, v);
+}
+
+// The upper (bf16 truncated) and the lower halves of two floats, and the floats
+// put together from them again.
+__device__ __forceinline__ u32 upper16x2(float a, float b)
+{
+    return __builtin_amdgcn_perm(__float_as_uint(b), __float_as_uint(a), 0x07060302u);
+}
+
+__device__ __forceinline__ u32 lower16x2(float a, float b)
+{
+    return __builtin_amdgcn_perm(__float_as_uint(b), __float_as_uint(a), 0x05040100u);
+}
+
+__device__ __forceinline__ float join16_0(u32 up, u32 low)
+{
+    return __uint_as_float(__builtin_amdgcn_perm(up, low, 0x05040100u));
+}
+
+__device__ __forceinline__ float join16_1(u32 up, u32 low)
+{
+    return __uint_as_float(__builtin_amdgcn_perm(up, low, 0x07060302u));
 }
 
 __device__ __forceinline__ u16 to_bf16(float f) { return static_cast<u16>(pack_bf16x2(f, 0.f)); }
@@ -342,6 +366,21 @@ __global__ __launch_bounds__(kTabThreads) void k_seq_order(const int4* __restric
     for (int e = threadIdx.x; e < n; e += kTabThreads) vorder[atomicAdd(&pos[depth(e)], 1)] = e;
 }
 
+// One Gram tile's four values of a lane to its place: rounded to bf16, or, with
+// gram_lo, in float32 as their upper halves there and their lower halves in
+// gram_lo.
+__device__ __forceinline__ void store_gram(const FusedParams& p, int64_t pos, f32x4_t v)
+{
+    uint2 packed;
+    if (p.gram_lo) {
+        packed = make_uint2(upper16x2(v[0], v[1]), upper16x2(v[2], v[3]));
+        *reinterpret_cast<uint2*>(p.gram_lo + pos) = make_uint2(lower16x2(v[0], v[1]), lower16x2(v[2], v[3]));
+    } else {
+        packed = make_uint2(pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]));
+    }
+    *reinterpret_cast<uint2*>(p.gram + pos) = packed;
+}
+
 // PACKED: a packed row, chunk positions from the chunk table.
 template <int N, bool PACKED>
 __global__ __launch_bounds__(kPrepThreads) void k_fused_prep(FusedParams p)
@@ -374,7 +413,7 @@ __global__ __launch_bounds__(kPrepThreads) void k_fused_prep(FusedParams p)
         const int64_t brow = p.G * N;
         const u16* Bchunk = static_cast<const u16*>(p.B) + ((b * p.T + c0) * p.G + g) * N;
         const u16* Cchunk = static_cast<const u16*>(p.C) + ((b * p.T + c0) * p.G + g) * N;
-        u16* gram = p.gram + ((static_cast<int64_t>(b) * p.G + g) * p.nC + c) * kTiles * 256;
+        const int64_t gram = ((static_cast<int64_t>(b) * p.G + g) * p.nC + c) * kTiles * 256;
         u16* bt = p.BT + ((static_cast<int64_t>(b) * p.G + g) * p.nC + c) * N * kQ;
         for (int part = blockIdx.z; part < kGramParts; part += gridDim.z) {
             if (part != static_cast<int>(blockIdx.z)) __syncthreads();   // the previous part's LDS reads are done
@@ -448,12 +487,7 @@ __global__ __launch_bounds__(kPrepThreads) void k_fused_prep(FusedParams p)
 #pragma unroll
             for (int kk = 0; kk < kNQ / 2; ++kk) {
                 const int j = (wave & 1) + 2 * kk;
-                if (j <= i) {
-                    uint2 packed;
-                    packed.x = pack_bf16x2(acc[kk][0], acc[kk][1]);
-                    packed.y = pack_bf16x2(acc[kk][2], acc[kk][3]);
-                    *reinterpret_cast<uint2*>(gram + (static_cast<int64_t>(tile_index(i, j)) * 64 + lane) * 4) = packed;
-                }
+                if (j <= i) store_gram(p, gram + (tile_index(i, j) * 64 + lane) * 4, acc[kk]);
             }
         }
     } else {
@@ -508,9 +542,9 @@ __global__ __launch_bounds__(kPrepThreads) void k_fused_prep(FusedParams p)
         }
         __syncthreads();
 
-        // ---- Gram tiles G^T[s][t] = sum_n B_s[n] C_t[n] (bf16), accumulator layout per lane.
+        // ---- Gram tiles G^T[s][t] = sum_n B_s[n] C_t[n], accumulator layout per lane.
         // Wavefront w: row rows[w / 2], s-tiles j = w%2, w%2 + 2, ...
-        u16* gram = p.gram + ((static_cast<int64_t>(b) * p.G + g) * p.nC + c) * kTiles * 256;
+        const int64_t gram = ((static_cast<int64_t>(b) * p.G + g) * p.nC + c) * kTiles * 256;
         {
             const int i = rows[wave >> 1];
             uint4 cfr[N / 32];
@@ -525,10 +559,7 @@ __global__ __launch_bounds__(kPrepThreads) void k_fused_prep(FusedParams p)
                     const uint4 va = *reinterpret_cast<const uint4*>(&sm.B[(16 * j + r) * RS + 32 * k + 8 * lg]);
                     acc = mfma(as_bf16x8(va), as_bf16x8(cfr[k]), acc);
                 }
-                uint2 packed;
-                packed.x = pack_bf16x2(acc[0], acc[1]);
-                packed.y = pack_bf16x2(acc[2], acc[3]);
-                *reinterpret_cast<uint2*>(gram + (static_cast<int64_t>(tile_index(i, j)) * 64 + lane) * 4) = packed;
+                store_gram(p, gram + (tile_index(i, j) * 64 + lane) * 4, acc);
             }
         }
 
@@ -600,8 +631,17 @@ __device__ __forceinline__ int x_tr_base(int f0, int lane)
     return 2 * xs_off(4 * lg + (j >> 2), f0 + 4 * (j & 3));
 }
 
-__device__ __forceinline__ void unpack4(uint2 gp, float* g)
+// (G32: gp holds the values' upper halves, gl their lower ones)
+template <bool G32>
+__device__ __forceinline__ void unpack4(uint2 gp, uint2 gl, float* g)
 {
+    if constexpr (G32) {
+        g[0] = join16_0(gp.x, gl.x);
+        g[1] = join16_1(gp.x, gl.x);
+        g[2] = join16_0(gp.y, gl.y);
+        g[3] = join16_1(gp.y, gl.y);
+        return;
+    }
     g[0] = __uint_as_float(gp.x << 16);
     g[1] = __uint_as_float(gp.x & 0xFFFF0000u);
     g[2] = __uint_as_float(gp.y << 16);
@@ -611,10 +651,11 @@ __device__ __forceinline__ void unpack4(uint2 gp, float* g)
 // Off-diagonal s-tile (entirely before the strip): the 1-SS mask factors as
 // exp2(cs_t - cs_end(j)) * exp2(cs_end(j) - cs_s), both factors <= 1, the
 // second folded with dt_s into vf.
-__device__ __forceinline__ void mask_off(uint2 gp, float u, float4 vf4, float* mv)
+template <bool G32>
+__device__ __forceinline__ void mask_off(uint2 gp, uint2 gl, float u, float4 vf4, float* mv)
 {
     float g[4];
-    unpack4(gp, g);
+    unpack4<G32>(gp, gl, g);
     mv[0] = g[0] * (u * vf4.x);
     mv[1] = g[1] * (u * vf4.y);
     mv[2] = g[2] * (u * vf4.z);
@@ -623,11 +664,12 @@ __device__ __forceinline__ void mask_off(uint2 gp, float u, float4 vf4, float* m
 
 // The strip's own s-tile: exp2(cs_t - cs_s) dt_s directly for s <= t, zero
 // above the diagonal (branch-free: exponent clamped, upper triangle selected away).
-__device__ __forceinline__ void mask_diag(uint2 gp, int t, int sb, float cst, float4 cs4, float4 dt4,
+template <bool G32>
+__device__ __forceinline__ void mask_diag(uint2 gp, uint2 gl, int t, int sb, float cst, float4 cs4, float4 dt4,
                                           float* mv)
 {
     float g[4];
-    unpack4(gp, g);
+    unpack4<G32>(gp, gl, g);
     const float csv[4] = {cs4.x, cs4.y, cs4.z, cs4.w}, dtv[4] = {dt4.x, dt4.y, dt4.z, dt4.w};
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
@@ -637,8 +679,9 @@ __device__ __forceinline__ void mask_diag(uint2 gp, int t, int sb, float cst, fl
 }
 
 // One K-step (s-tiles 2m, 2m+1) of strip S: masked Gram operand, 4 MFMAs.
-template <int S, int M>
-__device__ __forceinline__ void strip_step(const uint4* af, const char* gbase, int t, float cst,
+// gl: with G32, the lower halves of the two tiles' values.
+template <int S, int M, bool G32>
+__device__ __forceinline__ void strip_step(const uint4* af, const char* gbase, const uint2* gl, int t, float cst,
                                            float ce0, float ce1, float4 vf0, float4 vf1,
                                            const float* cs, const float* dt, int lg, f32x4_t* yv)
 {
@@ -647,17 +690,17 @@ __device__ __forceinline__ void strip_step(const uint4* af, const char* gbase, i
     const uint2 g0 = *reinterpret_cast<const uint2*>(gbase + j0 * 512);
     if constexpr (j1 < S) {
         const uint2 g1 = *reinterpret_cast<const uint2*>(gbase + j1 * 512);
-        mask_off(g0, __builtin_amdgcn_exp2f(cst - ce0), vf0, mv);
-        mask_off(g1, __builtin_amdgcn_exp2f(cst - ce1), vf1, mv + 4);
+        mask_off<G32>(g0, gl[0], __builtin_amdgcn_exp2f(cst - ce0), vf0, mv);
+        mask_off<G32>(g1, gl[1], __builtin_amdgcn_exp2f(cst - ce1), vf1, mv + 4);
     } else if constexpr (j1 == S) {
         const uint2 g1 = *reinterpret_cast<const uint2*>(gbase + j1 * 512);
         const int sb1 = 16 * j1 + 4 * lg;
-        mask_off(g0, __builtin_amdgcn_exp2f(cst - ce0), vf0, mv);
-        mask_diag(g1, t, sb1, cst, *reinterpret_cast<const float4*>(cs + sb1),
+        mask_off<G32>(g0, gl[0], __builtin_amdgcn_exp2f(cst - ce0), vf0, mv);
+        mask_diag<G32>(g1, gl[1], t, sb1, cst, *reinterpret_cast<const float4*>(cs + sb1),
                   *reinterpret_cast<const float4*>(dt + sb1), mv + 4);
     } else {   // j0 == S
         const int sb0 = 16 * j0 + 4 * lg;
-        mask_diag(g0, t, sb0, cst, *reinterpret_cast<const float4*>(cs + sb0),
+        mask_diag<G32>(g0, gl[0], t, sb0, cst, *reinterpret_cast<const float4*>(cs + sb0),
                   *reinterpret_cast<const float4*>(dt + sb0), mv);
 #pragma unroll
         for (int v = 4; v < 8; ++v) mv[v] = 0.f;
@@ -701,10 +744,17 @@ __device__ __forceinline__ void rf_step(const uint4* af, uint4 bt, const float* 
 // `mid` runs after K-step kMidStep, `fin` once the Gram rows have been read for
 // the last time.
 constexpr int kMidStep = 0;   // K-step after which `mid` runs (the next head's x copy)
-template <int W, int PTW, class Mid, class Fin>
+// G32: the Gram values are float32, their upper halves in GR and their lower
+// ones in global memory (gl, the same layout): 70 KB each, and only the upper
+// ones have room in LDS.  The lower halves of a K-step come from L2, requested
+// kLowAhead K-steps before it, and the next head's x after the last of them, so
+// that their wait does not include it.  At 2 x 4,096 tokens, 40 heads of 128, N
+// 128 the whole forward takes 128 us with them and 115 with a bf16 Gram matrix.
+constexpr int kLowAhead = 2;
+template <int W, int PTW, bool G32, class Mid, class Fin>
 __device__ __forceinline__ void diag_wave(const char* xsb, const int* xa, const float* cs,
                                           const float* vf, const float* dt, const float* wrf, const uint4* btf,
-                                          const u16* GR, int r, int lg, int lane, f32x4_t* yA, f32x4_t* yB,
+                                          const u16* GR, __amdgpu_buffer_rsrc_t gl, int r, int lg, int lane, f32x4_t* yA, f32x4_t* yB,
                                           f32x4_t* sacc, const Mid& mid, const Fin& fin)
 {
     constexpr int sA = W, sB = 15 - W;
@@ -713,6 +763,20 @@ __device__ __forceinline__ void diag_wave(const char* xsb, const int* xa, const 
     const float csA = cs[tA], csB = cs[tB];
     const char* gA = reinterpret_cast<const char*>(GR) + tile_index(sA, 0) * 512 + 8 * lane;
     const char* gB = reinterpret_cast<const char*>(GR) + tile_index(sB, 0) * 512 + 8 * lane;
+    uint2 lowA[G32 ? 2 * nB : 2], lowB[G32 ? 2 * nB : 2];
+    const auto load_low = [&](int m) {
+        const auto get = [&](int tile) {
+            return __builtin_bit_cast(uint2, __builtin_amdgcn_raw_buffer_load_b64(gl, 8 * lane, tile * 512, 0));
+        };
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            if (2 * m + k <= sB) lowB[2 * m + k] = get(tile_index(sB, 2 * m + k));
+            if (2 * m + k <= sA) lowA[2 * m + k] = get(tile_index(sA, 2 * m + k));
+        }
+    };
+    if constexpr (G32)
+#pragma unroll
+        for (int m = 0; m < kLowAhead && m < nB; ++m) load_low(m);
     const float* vfl = vf + 4 * lg;
     const char* x0 = xsb + xa[0];
     const char* x1 = xsb + xa[1];
@@ -748,12 +812,14 @@ __device__ __forceinline__ void diag_wave(const char* xsb, const int* xa, const 
             constexpr int m = Ms;
             Step nxt;
             if constexpr (m + 1 < nB) load(m + 1, nxt);
-            strip_step<sB, m>(cur.af, gB, tB, csB, cur.ce0, cur.ce1, cur.vf0, cur.vf1, cs, dt, lg, yB);
+            if constexpr (G32 && m + kLowAhead < nB) load_low(m + kLowAhead);
+            constexpr int ml = G32 ? 2 * m : 0;
+            strip_step<sB, m, G32>(cur.af, gB, lowB + ml, tB, csB, cur.ce0, cur.ce1, cur.vf0, cur.vf1, cs, dt, lg, yB);
             if constexpr (m < nA)
-                strip_step<sA, m>(cur.af, gA, tA, csA, cur.ce0, cur.ce1, cur.vf0, cur.vf1, cs, dt, lg, yA);
+                strip_step<sA, m, G32>(cur.af, gA, lowA + ml, tA, csA, cur.ce0, cur.ce1, cur.vf0, cur.vf1, cs, dt, lg, yA);
             if constexpr (m + 1 == nB) fin();   // this wavefront's Gram rows are read for the last time
             if constexpr (PTW > 0) rf_step<PTW, kPt0>(cur.af, btf[m], wrl, m, sacc);
-            if constexpr (m == kMidStep) mid();
+            if constexpr (m == (G32 ? nB - 1 : kMidStep)) mid();
             if constexpr (m + 1 < nB) cur = nxt;
         }(), ...);
     }(std::make_integer_sequence<int, nB>{});
@@ -770,19 +836,19 @@ __device__ __forceinline__ void diag_wave(const char* xsb, const int* xa, const 
                     af[kPt0 + i] = make_uint4(lo.x, lo.y, hi.x, hi.y);
                 }
                 rf_step<PTW, kPt0>(af, btf[m], wrl, m, sacc);
-                if constexpr (m == kMidStep) mid();
+                if constexpr (!G32 && m == kMidStep) mid();
             }(), ...);
         }(std::make_integer_sequence<int, kQ / 32 - nB>{});
     }
 }
 
-template <int PTW, class Mid, class Fin>
+template <int PTW, bool G32, class Mid, class Fin>
 __device__ __forceinline__ void diag_block(int wave, const char* xsb, const int* xa, const float* cs,
                                            const float* vf, const float* dt, const float* wrf, const uint4* btf,
-                                           const u16* GR, int r, int lg, int lane, f32x4_t* yA, f32x4_t* yB,
-                                           f32x4_t* sacc, const Mid& mid, const Fin& fin)
+                                           const u16* GR, __amdgpu_buffer_rsrc_t gl, int r, int lg, int lane, f32x4_t* yA,
+                                           f32x4_t* yB, f32x4_t* sacc, const Mid& mid, const Fin& fin)
 {
-#define SSD_DIAG_WAVE(W) diag_wave<W, PTW>(xsb, xa, cs, vf, dt, wrf, btf, GR, r, lg, lane, yA, yB, sacc, mid, fin)
+#define SSD_DIAG_WAVE(W) diag_wave<W, PTW, G32>(xsb, xa, cs, vf, dt, wrf, btf, GR, gl, r, lg, lane, yA, yB, sacc, mid, fin)
     switch (wave) {
     case 0: SSD_DIAG_WAVE(0); break;
     case 1: SSD_DIAG_WAVE(1); break;
@@ -926,14 +992,21 @@ __device__ __forceinline__ void dma_z_strips(const FusedParams& p, const Item& i
 }
 
 // dt of token `tid` (clamped to the chunk) of head hh of an item, raw bf16.
-// HSH = 1: headdim 128, the caller's head is two of the kernel's, which share
-// its dt, A, D and bias (a template argument: the shift and the other stride as
-// run-time values cost the plain kernels 0.5 %, and packed rows 3 %).
-template <int HSH>
+// G32 (the kernels for the other shapes): with headdim 128 the caller's head is
+// two of the kernel's, which share its dt, A, D and bias (head_shift; as a
+// run-time value it cost the plain kernels 0.5 %, and packed rows 3 %, so those
+// have none).
+template <bool G32>
+__device__ __forceinline__ int head_shift(const FusedParams& p)
+{
+    return G32 ? p.head128 : 0;
+}
+
+template <bool G32>
 __device__ __forceinline__ u16 load_dt(const FusedParams& p, const Item& it, int hh, int tid)
 {
     const int t = tid < it.L ? tid : it.L - 1;
-    return static_cast<const u16*>(p.dt)[(it.b * p.T + it.c0 + t) * (p.H >> HSH) + (hh >> HSH)];
+    return static_cast<const u16*>(p.dt)[(it.b * p.T + it.c0 + t) * (p.H >> head_shift<G32>(p)) + (hh >> head_shift<G32>(p))];
 }
 
 // The chunk's causal Gram tiles (shared by the item's heads) into LDS.
@@ -1010,7 +1083,7 @@ __device__ __forceinline__ void load_c_block(const FusedParams& p, const Item& i
 // recomputed for the block gradients, whose dy and dz need y before rounding).
 // FUSE: the right factor (of the first column block of the state, with two)
 // runs in the diagonal block's pass over x.
-template <int N, bool PACKED, bool EARLY, bool Y32, bool FUSE, int HSH>
+template <int N, bool PACKED, bool EARLY, bool Y32, bool FUSE, bool G32>
 __device__ __forceinline__ void head_step(const FusedParams& p, const Item& it, int hk, int& next, int nwork,
                                           int per_c, int nHG,
                                           uint4 (&btf)[kQ / 32], uint4 (&cf)[2][(N < kNH ? N : kNH) / 32],
@@ -1054,7 +1127,8 @@ __device__ __forceinline__ void head_step(const FusedParams& p, const Item& it, 
     const int b = it.b, c = it.c, L = it.L;
     const int64_t c0 = it.c0;
     const bool has_prev = it.has_prev, has_next = it.has_next;
-    const float Dh = Dp ? Dp[h >> HSH] : 0.f;   // scalar loads (read-only kernel arguments)
+    const int hsh = head_shift<G32>(p);
+    const float Dh = Dp ? Dp[h >> hsh] : 0.f;   // scalar loads (read-only kernel arguments)
     // this head's normalisation weights (one per thread of the first wavefront),
     // stored to LDS at the state barrier, read by the output stage
     const bool gate = p.z != nullptr, norm = p.norm_head != 0;
@@ -1065,12 +1139,12 @@ __device__ __forceinline__ void head_step(const FusedParams& p, const Item& it, 
     u16 dtr_next = 0;
     int h_next = -1, L_next = 0;   // the next head of this workgroup, once known
     if (!last) {
-        if (tid < kQ) dtr_next = load_dt<HSH>(p, it, h + 1, tid);
+        if (tid < kQ) dtr_next = load_dt<G32>(p, it, h + 1, tid);
         h_next = h + 1;
         L_next = L;
     } else if (hk > 0 && next < nwork) {
         const Item nit = decode_item<PACKED>(p, next, per_c, nHG, N);
-        if (tid < kQ) dtr_next = load_dt<HSH>(p, nit, nit.h0, tid);
+        if (tid < kQ) dtr_next = load_dt<G32>(p, nit, nit.h0, tid);
         h_next = nit.h0;
         L_next = nit.L;
     }
@@ -1094,12 +1168,12 @@ __device__ __forceinline__ void head_step(const FusedParams& p, const Item& it, 
             if (tid < Lh) {
                 dv = bf(raw);
                 if (p.dtx.active) {   // the block path's dt parameterisation
-                    if (biasp) dv += biasp[hh >> HSH];
+                    if (biasp) dv += biasp[hh >> hsh];
                     if (p.dtx.softplus) dv = softplus_f(dv);
                     dv = fminf(fmaxf(dv, p.dtx.lo), p.dtx.hi);
                 }
             }
-            inc = dv * (-expf(A_logp[hh >> HSH]) * kLog2e);
+            inc = dv * (-expf(A_logp[hh >> hsh]) * kLog2e);
             inc = wave_inclusive_scan(inc);
             if (lane == 63) wtv[wave] = inc;
         }
@@ -1185,17 +1259,20 @@ __device__ __forceinline__ void head_step(const FusedParams& p, const Item& it, 
     const auto gram_fin = [&] {
         if constexpr (kGramInPass) gram_refill();
     };
+    const __amdgpu_buffer_rsrc_t gram_low = __builtin_amdgcn_make_buffer_rsrc(
+        G32 ? p.gram_lo + ((static_cast<int64_t>(it.b) * p.G + it.g) * p.nC + it.c) * kTiles * 256 : nullptr, 0,
+        G32 ? kTiles * 512 : 0, 0x00020000);
     if constexpr (FUSE) {
         opaque_bt();
-        diag_block<PTW>(wave, reinterpret_cast<const char*>(xs), xa, cs, vf, dt, w, btf, gr, r, lg, lane, y[0], y[1],
-                        sacc[0], next_x, gram_fin);
+        diag_block<PTW, G32>(wave, reinterpret_cast<const char*>(xs), xa, cs, vf, dt, w, btf, gr, gram_low, r, lg, lane,
+                             y[0], y[1], sacc[0], next_x, gram_fin);
         // (two column blocks: the first block's right factor was fused; the
         // second block's B^T fragments now -- requested during the diagonal
         // block they would hold registers it needs)
         if constexpr (HALVES > 1) load_bt_block<N, NH>(p, it, ntw, r, lg, 1, bth);
     } else {
-        diag_block<0>(wave, reinterpret_cast<const char*>(xs), xa, cs, vf, dt, w, btf, gr, r, lg, lane, y[0], y[1],
-                      sacc[0], [] {}, [] {});
+        diag_block<0, G32>(wave, reinterpret_cast<const char*>(xs), xa, cs, vf, dt, w, btf, gr, gram_low, r, lg, lane,
+                           y[0], y[1], sacc[0], [] {}, [] {});
     }
     if constexpr (!kGramInPass) gram_refill();
     if constexpr (!FUSE) next_x();
@@ -1378,7 +1455,7 @@ __device__ __forceinline__ void head_step(const FusedParams& p, const Item& it, 
                 const Item nit = decode_item<PACKED>(p, next, per_c, nHG, N);
                 dma_gram(gr, p, nit, wave, dmo);
                 dma_head(p, nit, nit.h0, xs_n, wave, dmo);
-                if (tid < kQ) dtr_next = load_dt<HSH>(p, nit, nit.h0, tid);
+                if (tid < kQ) dtr_next = load_dt<G32>(p, nit, nit.h0, tid);
             }
         }
 
@@ -1525,7 +1602,7 @@ __device__ __forceinline__ void head_step(const FusedParams& p, const Item& it, 
 
 // A_log, D and the dt bias come as separate read-only arguments so that their per-head values
 // are scalar loads (a vector load would wait behind the outstanding copies).
-template <int N, bool PACKED, bool EARLY, bool Y32, bool FUSE, int HSH>
+template <int N, bool PACKED, bool EARLY, bool Y32, bool FUSE, bool G32>
 __global__ __launch_bounds__(kMainThreads, 1) void k_fused_main(FusedParams p, const float* __restrict__ A_logp,
                                                                 const float* __restrict__ Dp,
                                                                 const float* __restrict__ biasp)
@@ -1567,7 +1644,7 @@ __global__ __launch_bounds__(kMainThreads, 1) void k_fused_main(FusedParams p, c
         const Item it = decode_item<PACKED>(p, work, per_c, nHG, N);
         dma_gram(s_gr, p, it, wave, dmo);
         dma_head(p, it, it.h0, sm.XS[0], wave, dmo);
-        if (tid < kQ) dtr = load_dt<HSH>(p, it, it.h0, tid);
+        if (tid < kQ) dtr = load_dt<G32>(p, it, it.h0, tid);
     }
     wait_vmem();
     __syncthreads();
@@ -1587,7 +1664,7 @@ __global__ __launch_bounds__(kMainThreads, 1) void k_fused_main(FusedParams p, c
     const Item it = decode_item<PACKED>(p, work, per_c, nHG, N);
     int next = nwork;
     for (int hk = 0; hk < p.HG; ++hk) {
-        head_step<N, PACKED, EARLY, Y32, FUSE, HSH>(p, it, hk, next, nwork, per_c, nHG, btf, cf, dtr, ready, sm.XS[q],
+        head_step<N, PACKED, EARLY, Y32, FUSE, G32>(p, it, hk, next, nwork, per_c, nHG, btf, cf, dtr, ready, sm.XS[q],
                      sm.XS[q ^ 1], sm.cs[q], sm.dt[q], sm.wtot[q], sm.vf[q], sm.w[q], sm.cs[q ^ 1], sm.dt[q ^ 1],
                      sm.wtot[q ^ 1], sm.vf[q ^ 1], sm.w[q ^ 1], s_gr, s_hb, &sm.ticket, A_logp, Dp, biasp, sm.wn);
         q ^= 1;
@@ -1600,7 +1677,8 @@ __global__ __launch_bounds__(kMainThreads, 1) void k_fused_main(FusedParams p, c
 template <int N>
 hipError_t launch_n(const FusedParams& p, hipStream_t stream, hipEvent_t ev_begin, hipEvent_t ev_end)
 {
-    if (p.y32 && (p.vtab || p.z || p.norm_head || p.head128)) return hipErrorInvalidValue;   // plain rows, no gate/norm
+    if (p.y32 && (p.vtab || p.z || p.norm_head || p.gram_lo)) return hipErrorInvalidValue;   // plain rows, no gate/norm
+    if (p.head128 && !p.gram_lo) return hipErrorInvalidValue;
     if (p.vtab) {   // packed row: the chunk table first
         hipError_t e = launch_seq_table(p.seq_idx, p.arg_starts, p.T, p.nseq, kQ, p.nC, p.ring_rows, p.starts,
                                         p.vtab, nullptr, p.vcount, stream);
@@ -1636,29 +1714,30 @@ hipError_t launch_n(const FusedParams& p, hipStream_t stream, hipEvent_t ev_begi
     const auto go = [&](auto kern) {
         hipLaunchKernelGGL(kern, g_main, dim3(kMainThreads), 0, stream, p, p.A_log, p.D, p.dtx.bias);
     };
-    const auto pick = [&](auto hsh) {
-        constexpr int HSH = decltype(hsh)::value;
-        if (p.vtab && p.early_flag)
-            go(k_fused_main<N, true, true, false, false, HSH>);
-        else if (p.vtab && p.fuse_rf)
-            go(k_fused_main<N, true, false, false, true, HSH>);
-        else if (p.vtab)
-            go(k_fused_main<N, true, false, false, false, HSH>);
-        else if (p.early_flag)
-            go(k_fused_main<N, false, true, false, false, HSH>);
-        else if (p.fuse_rf)
-            go(k_fused_main<N, false, false, false, true, HSH>);
-        else
-            go(k_fused_main<N, false, false, false, false, HSH>);
-    };
     if (p.y32 && p.early_flag)
-        go(k_fused_main<N, false, true, true, false, 0>);
+        go(k_fused_main<N, false, true, true, false, false>);
     else if (p.y32)
-        go(k_fused_main<N, false, false, true, false, 0>);
-    else if (p.head128)
-        pick(std::integral_constant<int, 1>{});
+        go(k_fused_main<N, false, false, true, false, false>);
+    else if (p.gram_lo && p.vtab && p.early_flag)
+        go(k_fused_main<N, true, true, false, false, true>);
+    else if (p.gram_lo && p.vtab)
+        go(k_fused_main<N, true, false, false, false, true>);
+    else if (p.gram_lo && p.early_flag)
+        go(k_fused_main<N, false, true, false, false, true>);
+    else if (p.gram_lo)
+        go(k_fused_main<N, false, false, false, false, true>);
+    else if (p.vtab && p.early_flag)
+        go(k_fused_main<N, true, true, false, false, false>);
+    else if (p.vtab && p.fuse_rf)
+        go(k_fused_main<N, true, false, false, true, false>);
+    else if (p.vtab)
+        go(k_fused_main<N, true, false, false, false, false>);
+    else if (p.early_flag)
+        go(k_fused_main<N, false, true, false, false, false>);
+    else if (p.fuse_rf)
+        go(k_fused_main<N, false, false, false, true, false>);
     else
-        pick(std::integral_constant<int, 0>{});
+        go(k_fused_main<N, false, false, false, false, false>);
     err = hipGetLastError();
     if (err == hipSuccess && ev_end) err = hipEventRecord(ev_end, stream);
     return err;
@@ -1693,7 +1772,7 @@ bool fused_supported(int64_t H, int64_t P, int64_t N, bool bf16)
     return bf16 && (P == kP || (P == 2 * kP && 2 * H <= 65535)) && (N == 64 || N == 128 || N == 256);
 }
 
-FusedLayout fused_layout(int64_t b, int64_t T, int64_t H, int64_t N, int64_t G, int64_t nC, int64_t nseq)
+FusedLayout fused_layout(int64_t b, int64_t T, int64_t H, int64_t N, int64_t G, int64_t nC, int64_t nseq, bool gram32)
 {
     auto al = [](size_t v) { return (v + 255) / 256 * 256; };
     FusedLayout w;
@@ -1705,6 +1784,8 @@ FusedLayout fused_layout(int64_t b, int64_t T, int64_t H, int64_t N, int64_t G, 
     size_t off = kWorkspaceHeader;   // the status word sits in the header
     w.gram = off;
     off = al(off + sizeof(u16) * static_cast<size_t>(b * G * w.nC) * kTiles * 256);
+    w.gram_lo = off;
+    if (gram32) off = al(off + sizeof(u16) * static_cast<size_t>(b * G * w.nC) * kTiles * 256);
     w.BT = off;
     off = al(off + sizeof(u16) * static_cast<size_t>(b * G * w.nC) * static_cast<size_t>(N * kQ));
     w.ring = off;

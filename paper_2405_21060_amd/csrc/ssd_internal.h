@@ -101,6 +101,9 @@ struct FusedParams {
     float* fin;
     // workspace
     uint16_t* gram;   // (b, G, nC, tiles, 64 lanes, 4) causal Gram tiles, bf16, per-lane layout
+    // not null: the Gram values are float32, gram holding the upper and gram_lo
+    // the lower 16 bits of each
+    uint16_t* gram_lo = nullptr;
     uint16_t* BT;     // (b, G, nC, N, Q) B^T per chunk, bf16
     float* ring;      // (b, H, 2, P, N) chunk-state ring
     int* flags;       // (b, H, nC)      state-published flags
@@ -144,7 +147,7 @@ struct FusedParams {
 };
 
 struct FusedLayout {
-    size_t gram, BT, ring, flags, ticket, starts, vtab, vorder, total;
+    size_t gram, gram_lo, BT, ring, flags, ticket, starts, vtab, vorder, total;
     int64_t nC;          // chunks the layout holds (table capacity for a packed row)
     int64_t ring_rows;   // rows of the state ring
 };
@@ -163,7 +166,7 @@ hipError_t launch_seq_table(const int32_t* seq_idx, const SeqStartsArg* arg_star
                             hipStream_t stream);
 // nseq > 0: layout for one packed row of nseq sequences (seq_idx); nC is the
 // row's chunk count ceil(T / Q) either way.
-FusedLayout fused_layout(int64_t b, int64_t T, int64_t H, int64_t N, int64_t G, int64_t nC, int64_t nseq);
+FusedLayout fused_layout(int64_t b, int64_t T, int64_t H, int64_t N, int64_t G, int64_t nC, int64_t nseq, bool gram32);
 hipError_t launch_fused(const FusedParams& p, hipStream_t stream, hipEvent_t ev_begin,
                         hipEvent_t ev_end);
 

@@ -7,6 +7,7 @@ Against the float64 oracle, at the bounds of test_gpu_parity.
 import numpy as np
 import pytest
 
+import oracle
 import oracle.block as ob
 from paper_2405_21060_amd.inputs import Problem, make_block_inputs, make_inputs
 from tests.ssd_harness import TOL, announce, rel_err, run_gpu, to_device, to_f64
@@ -114,3 +115,31 @@ def test_workspace_of_the_general_size_is_enough(tune):
         assert rc == want
     torch.cuda.synchronize()
     compare(inp, y, fin)
+
+
+@pytest.mark.parametrize("P,Q,N,packed", [(128, 256, 128, False), (128, 64, 64, True), (64, 128, 128, False),
+                                          (64, 32, 256, True)])
+def test_scores_are_rounded_once(P, Q, N, packed):
+    """The Gram matrix of these shapes is float32: a score C_t . B_s times its
+    decay and dt_s is rounded to bf16 once, as a matrix operand.  With x = 1 at
+    one token of a chunk and zero at the others (no skip term, no state), y_t is
+    that one operand exactly, so its error is at most half a unit in the last
+    place, 2^-8 of the value (and 2^-13 for the decay's float32 exponent and the
+    sum over N, whose terms have one sign).  Rounded twice it comes near 2^-7."""
+    from paper_2405_21060_amd.inputs import f32_to_bf16_bits
+
+    announce("one rounding, P%d Q%d N%d packed %s" % (P, Q, N, packed))
+    T = 512 if packed else 256
+    inp = make_inputs(Problem(1 if packed else 2, T, 3, P, N, 1, Q, "bf16", varlen=packed, len_lo=256, len_hi=256), 16)
+    rng = np.random.default_rng(17)
+    inp.A_log[:] = rng.uniform(-1.0, 0.0, 3)
+    inp.dt[:] = f32_to_bf16_bits(rng.uniform(0.01, 0.05, inp.dt.shape))
+    inp.B[:] = inp.B & 0x7FFF
+    inp.C[:] = inp.C & 0x7FFF
+    inp.x[:] = 0
+    inp.x[:, 0::256] = 0x3F80   # one token of each chunk
+    y, _ = run_gpu(inp, use_D=False)
+    inp.D = np.zeros_like(inp.D)
+    ref, _ = oracle.forward_inputs(inp)
+    assert ref.min() > 0
+    assert (np.abs(to_f64(y) - ref) / ref).max() <= 2.0 ** -8 + 2.0 ** -13
