@@ -181,7 +181,7 @@ bool fused_shape(const ssd::Shape& s)
 // kernels where an operand is not 16-byte aligned or the workspace holds only
 // the general layout (fixed scratch sized for it): what those took stays taken.
 // Elsewhere the fused ones are the faster (2 x 4096 tokens, 40 heads of 128,
-// N 128: 128 us against 607 on the general kernels).
+// N 128: 132 us against 607 on the general kernels).
 bool fused_only(const ssd::Shape& s) { return fused_shape(s) && fused_own(s); }
 
 size_t general_bytes(const ssd::Shape& s)

@@ -6,7 +6,8 @@
 // depend on it); plain rows, or one packed row of sequences (Section
 // 8.3) through a chunk table built on the device.  At P = 64 called with Q = 256
 // the Gram matrix is held in bf16; at the other shapes (G32) in float32, so that
-// a score is rounded once, after its mask, as the general kernels do it there.
+// a score is rounded once, after its mask, and the operand of the right factor
+// that is rounded is the weighted x, not the weighted B.
 //
 // Two launches per call (a packed row adds the small kernels that build and
 // order its chunk table).
@@ -749,7 +750,7 @@ constexpr int kMidStep = 0;   // K-step after which `mid` runs (the next head's 
 // ones have room in LDS.  The lower halves of a K-step come from L2, requested
 // kLowAhead K-steps before it, and the next head's x after the last of them, so
 // that their wait does not include it.  At 2 x 4,096 tokens, 40 heads of 128, N
-// 128 the whole forward takes 128 us with them and 115 with a bf16 Gram matrix.
+// 128 they took the whole forward from 115 us (bf16 Gram matrix) to 128.
 constexpr int kLowAhead = 2;
 template <int W, int PTW, bool G32, class Mid, class Fin>
 __device__ __forceinline__ void diag_wave(const char* xsb, const int* xa, const float* cs,
@@ -1297,6 +1298,28 @@ __device__ __forceinline__ void head_step(const FusedParams& p, const Item& it, 
         }
     }
 
+    // With G32 the weighted x is the rounded operand of the right factor
+    // (elsewhere the weighted B): x w in place, once for all wavefronts, every
+    // reader of x itself being done (two barriers and a pass over 32 KB: 128 ->
+    // 132 us at 2 x 4,096 tokens, 40 heads of 128, N 128).
+    if constexpr (G32) {
+        lds_barrier();
+#pragma unroll
+        for (int k = 0; k < kQ * kP / 8 / kMainThreads; ++k) {
+            const int i = tid + kMainThreads * k;   // 16-byte piece; eight to a token's row
+            uint4* const piece = reinterpret_cast<uint4*>(xs) + i;
+            const float ws = w[i >> 3];
+            const uint4 v = *piece;
+            const u32 in[4] = {v.x, v.y, v.z, v.w};
+            u32 o[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                o[e] = pack_bf16x2(__uint_as_float(in[e] << 16) * ws, __uint_as_float(in[e] & 0xFFFF0000u) * ws);
+            *piece = make_uint4(o[0], o[1], o[2], o[3]);
+        }
+        lds_barrier();
+    }
+
     // ---- right factor (of the blocks not fused above): S[p][n] = sum_s x[s][p]
     // w_s B[s][n], this wavefront's tiles, per column block of the state
     if constexpr (!FUSE) opaque_bt();
@@ -1309,17 +1332,22 @@ __device__ __forceinline__ void head_step(const FusedParams& p, const Item& it, 
         const float* wl = w + 4 * lg;
 #pragma unroll
         for (int m = 0; m < kQ / 32; ++m) {
-            const float4 w0 = *reinterpret_cast<const float4*>(wl + 32 * m);
-            const float4 w1 = *reinterpret_cast<const float4*>(wl + 32 * m + 16);
-            const float wv[8] = {w0.x, w0.y, w0.z, w0.w, w1.x, w1.y, w1.z, w1.w};
-            const u32 bw[4] = {bsrc[m].x, bsrc[m].y, bsrc[m].z, bsrc[m].w};
-            float bf8[8];
+            bf16x8_t bop;
+            if constexpr (G32) {
+                bop = as_bf16x8(bsrc[m]);
+            } else {
+                const float4 w0 = *reinterpret_cast<const float4*>(wl + 32 * m);
+                const float4 w1 = *reinterpret_cast<const float4*>(wl + 32 * m + 16);
+                const float wv[8] = {w0.x, w0.y, w0.z, w0.w, w1.x, w1.y, w1.z, w1.w};
+                const u32 bw[4] = {bsrc[m].x, bsrc[m].y, bsrc[m].z, bsrc[m].w};
+                float bf8[8];
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                bf8[2 * e] = __uint_as_float(bw[e] << 16) * wv[2 * e];
-                bf8[2 * e + 1] = __uint_as_float(bw[e] & 0xFFFF0000u) * wv[2 * e + 1];
+                for (int e = 0; e < 4; ++e) {
+                    bf8[2 * e] = __uint_as_float(bw[e] << 16) * wv[2 * e];
+                    bf8[2 * e + 1] = __uint_as_float(bw[e] & 0xFFFF0000u) * wv[2 * e + 1];
+                }
+                bop = pack8(bf8);
             }
-            const bf16x8_t bop = pack8(bf8);
 #pragma unroll
             for (int i = 0; i < PTW; ++i) {
                 const char* xb = xsb + xa[pt0 + i] + 4096 * m;

@@ -143,3 +143,25 @@ def test_scores_are_rounded_once(P, Q, N, packed):
     ref, _ = oracle.forward_inputs(inp)
     assert ref.min() > 0
     assert (np.abs(to_f64(y) - ref) / ref).max() <= 2.0 ** -8 + 2.0 ** -13
+
+
+@pytest.mark.parametrize("P,N", [(128, 128), (128, 256), (128, 64)])
+def test_final_states_round_the_weighted_x(P, N):
+    """The rounded operand of the state update at these shapes is x_s dt_s
+    exp(cs_end - cs_s).  Against that sum in float64 the final states differ
+    where the float32 weight (relative error about 2^-20) lands on the other
+    side of a rounding: a share of 2^-20 / 2^-8 of the operands, by 2^-8 of
+    their value, so 2^-14 of the norm, and the sum's own float32 rounding; four
+    times that is asked for.  Another operand rounded gives 2e-3."""
+    from paper_2405_21060_amd.inputs import bf16_bits_to_f32, f32_to_bf16_bits
+
+    announce("weighted x, P%d N%d" % (P, N))
+    inp = make_inputs(Problem(2, 250, 3, P, N, 1, 256, "bf16"), 18)
+    inp.A_log[:] = np.random.default_rng(19).uniform(-1.0, 0.0, 3)
+    _, fin = run_gpu(inp)
+    x, dt, B = (inp.as_f64(k) for k in ("x", "dt", "B"))
+    cs = np.cumsum(dt * -np.exp(inp.A_log.astype(np.float64)), 1)
+    xw = (x * (dt * np.exp(cs[:, -1:] - cs))[..., None]).astype(np.float32)
+    xw = bf16_bits_to_f32(f32_to_bf16_bits(xw)).astype(np.float64)
+    ref = np.matmul(xw.transpose(0, 2, 3, 1), B[:, :, 0][:, None])
+    assert np.linalg.norm(to_f64(fin) - ref) <= 4 * 2.0 ** -14 * np.linalg.norm(ref)
