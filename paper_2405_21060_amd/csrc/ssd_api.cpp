@@ -176,13 +176,21 @@ bool fused_shape(const ssd::Shape& s)
     return ssd::tuning(ssd::kTuneForceGeneral) != 1 && ssd::fused_supported(s.H, s.P, s.N, s.bf16);
 }
 
-// The fused kernels' own shape (headdim 64, chunks of 256): always theirs.
-// Their other shapes (headdim 128, shorter chunks) fall back to the general
-// kernels where an operand is not 16-byte aligned or the workspace holds only
-// the general layout (fixed scratch sized for it): what those took stays taken.
-// Elsewhere the fused ones are the faster (2 x 4096 tokens, 40 heads of 128,
-// N 128: 132 us against 607 on the general kernels).
+// The fused kernels' own shape: always theirs.  Their other shapes fall back to
+// the general kernels where an operand is not 16-byte aligned or the workspace
+// holds only the general layout (fixed scratch sized for it): what those took
+// stays taken; and on packed rows of very short sequences (fused_pays).
 bool fused_only(const ssd::Shape& s) { return fused_shape(s) && fused_own(s); }
+
+// Where the fused kernels are the faster at their other shapes.  Plain rows:
+// everywhere (N 128, us against the general kernels': 8 heads of 128, one token
+// 21 / 30; 80 heads of 128, 64 rows of 64 tokens 355 / 2,045; 40 heads of 128, 2
+// x 4,096 tokens 132 / 607; headdim 64 with chunks of 64, 8 heads, 777 tokens 27 /
+// 35, 80 heads, 256 rows of 16 tokens 702 / 2,640).  A packed row costs a chunk
+// of 256 tokens' work per sequence: at 4,096 tokens, 24 heads of 128, sequences
+// of 16 tokens 485 / 452, of 24 347 / 433; of 64 with chunks of 64 262 / 201 and
+// 187 / 205.  (With host offsets the general kernels would run once a sequence.)
+bool fused_pays(const ssd::Shape& s, int64_t nseq) { return nseq == 0 || s.T >= 24 * nseq; }
 
 size_t general_bytes(const ssd::Shape& s)
 {
@@ -197,7 +205,8 @@ void forward_needs(const ssd_problem* prob, const ssd::Shape& s, size_t* least, 
     *least = *best = general;
     if (!fused_shape(s)) return;
     size_t fused = fused_plan(s, 0).total;
-    if (fused_packed_ok(prob))   // a packed row of prob->nseq sequences (when seq_idx is passed) needs its chunk table
+    // a packed row of prob->nseq sequences (when seq_idx is passed) needs its chunk table
+    if (fused_packed_ok(prob) && (fused_only(s) || fused_pays(s, prob->nseq)))
         fused = std::max(fused, fused_plan(s, prob->nseq).total);
     else if (prob->batch == 1 && prob->nseq >= 1 && prob->nseq <= prob->seqlen)
         fused = std::max(fused, general);   // a packed row the fused kernels cannot index
@@ -282,7 +291,7 @@ int forward_impl(const ssd_problem* prob, const ssd_block_opts* opts, const void
     const bool post = gn.z || gn.group > 0;
     bool fused = arg_starts || (fused_shape(s) && (!seq_idx || fused_packed_ok(prob)));
     if (fused && !arg_starts && !fused_only(s))
-        fused = workspace_bytes >= fused_plan(s, seq_idx ? s.nseq : 0).total && aligned16(x) && aligned16(B) &&
+        fused = fused_pays(s, seq_idx ? s.nseq : 0) && workspace_bytes >= fused_plan(s, seq_idx ? s.nseq : 0).total && aligned16(x) && aligned16(B) &&
                 aligned16(C) && aligned16(y);   // (z: checked with the block's options)
     // status word: in the workspace's header unless the caller keeps it elsewhere
     if (!status) status = static_cast<int*>(workspace);

@@ -58,6 +58,22 @@ def test_packed_rows(P, N, G, Q, host):
                                      initial_states=d["initial_states"]))
 
 
+@pytest.mark.parametrize("P,Q", [(128, 256), (64, 64)])
+@pytest.mark.parametrize("length,general", [(16, True), (32, False)])
+def test_short_packed_sequences_stay_general(tune, P, Q, length, general):
+    """A chunk per sequence costs the fused kernels 256 tokens' work: rows of
+    sequences shorter than 24 tokens on average run on the general kernels."""
+    import torch
+
+    announce("packed, sequences of %d, P%d Q%d" % (length, P, Q))
+    inp = _inputs(1, 500, 3, P, 128, 1, Q, seed=20, varlen=True, len_lo=length, len_hi=length)
+    y, fin = run_gpu(inp)
+    compare(inp, y, fin)
+    tune("force_general_path", 1)
+    y2, fin2 = run_gpu(inp)
+    assert (torch.equal(y, y2) and torch.equal(fin, fin2)) == general
+
+
 @pytest.mark.parametrize("group", [0, 128, 512])
 def test_block_headdim_128(group):
     announce("fused route, block P128 norm group %d" % group)
