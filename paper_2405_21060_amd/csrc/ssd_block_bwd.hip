@@ -527,10 +527,20 @@ hipError_t out_side(const BlockBwdParams& p, hipStream_t st)
         return hipGetLastError();
     }
     const int64_t pieces = p.group / 8;
-    if (pieces > 128 && pieces <= 1024) {   // wide groups (128 pieces are two a lane of one wavefront)
+    const int64_t nch = (p.rows + kRowsPerChunk - 1) / kRowsPerChunk;
+    // Wide groups (128 pieces are two a lane of one wavefront): a workgroup per
+    // chunk of 16 rows, one row after the other, pays where the workgroups are
+    // many or the rows of the only chunk few; between them a wavefront per row
+    // and group.  Whole block backward, us, against the wavefronts': bf16, one
+    // group of 5,120 channels, 2 rows 76 / 92, 8 95 / 98, 16 122 / 107, 64 127 /
+    // 115, 777 183 / 179, 1,280 185 / 186, 4,096 395 / 447; of 1,536 channels, 64
+    // rows 81 / 78, 777 111 / 111, 1,536 134 / 136; float32, 5,120 channels, 16
+    // rows 156 / 151, 128 185 / 183, 777 423 / 427; 1,536 channels, 64 rows 117 / 118.
+    constexpr int64_t kMostRowsAlone = 8, kLeastGroups = sizeof(T) == 2 ? 80 : 16;
+    const bool wide = p.rows <= kMostRowsAlone || nch * (p.C / p.group) >= kLeastGroups;
+    if (wide && pieces > 128 && pieces <= 1024) {
         const int k = pieces > 512 ? 2 : 1;
         const dim3 threads(static_cast<unsigned>(((pieces + k - 1) / k + 63) / 64 * 64));
-        const int64_t nch = (p.rows + kRowsPerChunk - 1) / kRowsPerChunk;
         const dim3 grid(static_cast<unsigned>(nch), static_cast<unsigned>(p.C / p.group));
         const auto go = [&](auto kern) { hipLaunchKernelGGL(kern, grid, threads, 0, st, p); };
         if (p.dw)
@@ -552,7 +562,6 @@ hipError_t out_side(const BlockBwdParams& p, hipStream_t st)
     const int64_t ngroups = p.rows * (p.C / p.group);
     const dim3 grid(static_cast<unsigned>((ngroups + per_block - 1) / per_block));
     const int64_t per_lane = (pieces + seg - 1) / seg;
-    const int64_t nch = (p.rows + kRowsPerChunk - 1) / kRowsPerChunk;
     if (p.dw && per_lane <= 2) {   // weight gradient folded in: y, z, dout read once
         const int64_t gpr = p.C / p.group;
         const dim3 g2(static_cast<unsigned>((gpr + per_block - 1) / per_block), static_cast<unsigned>(nch));

@@ -39,3 +39,23 @@ def test_wide_groups(H, P, G, group, gate, weight, dtype):
     for k in ("dx", "dA_log", "dB", "dC", "ddt_bias") + (("dz",) if gate else ()) + (("dnorm_weight",) if weight else ()):
         check(k, got[k], ref[k], TOL[dtype])
     check("ddt_raw", got["ddt"], ref["ddt_raw"], TOL[dtype])
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("gate,weight", [(True, True), (False, False)])
+@pytest.mark.parametrize("rows,H,P,G,group", [
+    (8, 65, 64, 1, 4160), (9, 65, 64, 1, 4160),          # one chunk: few rows, too many
+    (240, 65, 16, 1, 1040), (241, 65, 16, 1, 1040),      # 15 and 16 workgroups
+    (1264, 65, 16, 1, 1040), (1265, 65, 16, 1, 1040),    # 79 and 80
+    (640, 130, 16, 2, 1040)])                            # 40 chunks of two groups
+def test_row_counts(rows, H, P, G, group, gate, weight, dtype):
+    """Rows on both sides of the lines where the gradient's kernels change."""
+    announce("norm group %d, %d rows %s gate %s weight %s" % (group, rows, dtype, gate, weight))
+    p = Problem(1, rows, H, P, 64, G, 256, dtype)
+    bi = make_block_inputs(p, 43)
+    o = dict(BASE, gate=gate, weight=weight, group=group, dt_raw=bi.dt_raw)
+    dout, _ = make_grad_inputs(p, 43)
+    got, ref = run_gpu(bi, dout, None, o), run_oracle(bi, dout, None, o)
+    for k in ("dx", "dA_log", "dB", "dC", "ddt_bias") + (("dz",) if gate else ()) + (("dnorm_weight",) if weight else ()):
+        check(k, got[k], ref[k], TOL[dtype])
+    check("ddt_raw", got["ddt"], ref["ddt_raw"], TOL[dtype])
