@@ -69,12 +69,22 @@ struct Vec8<float> {
 
 __device__ __forceinline__ float silu_f(float z) { return z / (1.f + expf(-z)); }
 
-// The same by v_exp_f32 and v_rcp_f32 (1 ulp each), for results that are rounded
-// to bf16 (as in the fused chunk kernel's output stage); z of large magnitude
-// gives 0 or z, as above.
-__device__ __forceinline__ float silu_fast(float z)
+// The same, as exact, for |z| < 87 with z a bf16 value, on v_exp_f32 and
+// v_rcp_f32 without the range handling of expf and of the division.  exp(-z) =
+// 2^t (1 + r): t is z times the first 16 bits of log2(e), exact (8 bits times
+// 16), and r the rest (up to 4.3e-4; r^2 / 2 is below float32's precision); the
+// quotient is corrected by its remainder once.  Relative error at most 2.5e-7
+// (silu_f 1.7e-7); with t = z log2(e) rounded and no remainder it was 4e-6.
+constexpr float kSiluHwMax = 87.f;
+
+__device__ __forceinline__ float silu_hw(float z)
 {
-    return z * __builtin_amdgcn_rcpf(1.f + __builtin_amdgcn_exp2f(-z * kLog2e));
+    constexpr float kLog2eUp = 47274.f / 32768.f;
+    constexpr float kLow = (1.4426950408889634 - 47274. / 32768.) * 0.6931471805599453;
+    const float e = __builtin_amdgcn_exp2f(-z * kLog2eUp);
+    const float d = 1.f + fmaf(e, -z * kLow, e);
+    const float inv = __builtin_amdgcn_rcpf(d), q = z * inv;
+    return fmaf(fmaf(-d, q, z), inv, q);
 }
 
 // Gated piece: y, times SiLU(z) when gating.
@@ -174,9 +184,10 @@ __global__ __launch_bounds__(kGateNormThreads) void k_gate_norm(GateNormParams p
 // workgroup of up to 512 threads per (row, group) and K (1 or 2) pieces per
 // thread, all loads of y and z in flight at once, one sum over the workgroup.
 // Memory-bound: reads y and z and writes y once.  At 16,384 rows of 5,120
-// channels, bf16, one group: 92 us for 503 MB, where one wavefront per group
-// (ten pieces a lane, 84 registers) took 149; with the full-precision division
-// and exponential in the gate 109 us (the vector unit bounds it then).
+// channels, bf16, one group: 98 us for 503 MB, where one wavefront per group
+// (ten pieces a lane, 84 registers) took 149; with expf and a full division in
+// the gate 109 (the vector unit bounds it then), with a gate of less than
+// float32's precision 92.
 template <typename T, int K>
 __global__ __launch_bounds__(512) void k_gate_norm_wide(GateNormParams p)
 {
@@ -196,12 +207,21 @@ __global__ __launch_bounds__(512) void k_gate_norm_wide(GateNormParams p)
         float ss = 0.f;
 #pragma unroll
         for (int k = 0; k < K; ++k)
-            if (tid + k * nt < pieces)
+            if (tid + k * nt < pieces) {
+                if (p.z) {
+                    float zmax = 0.f;   // (a NaN passes, and gives NaN)
 #pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    if (p.z) g[k][e] *= sizeof(T) == 2 ? silu_fast(zv[k][e]) : silu_f(zv[k][e]);
-                    ss += g[k][e] * g[k][e];
+                    for (int e = 0; e < 8; ++e) zmax = fmaxf(zmax, fabsf(zv[k][e]));
+                    if (sizeof(T) == 2 && zmax < kSiluHwMax)
+#pragma unroll
+                        for (int e = 0; e < 8; ++e) g[k][e] *= silu_hw(zv[k][e]);
+                    else
+#pragma unroll
+                        for (int e = 0; e < 8; ++e) g[k][e] *= silu_f(zv[k][e]);
                 }
+#pragma unroll
+                for (int e = 0; e < 8; ++e) ss += g[k][e] * g[k][e];
+            }
         ss = wave_sum(ss);
         if ((tid & 63) == 0) part[slot][tid >> 6] = ss;
         __syncthreads();   // (the other slot is rewritten only after the next group's barrier)

@@ -4,6 +4,7 @@ gradient change kernels: 128 pieces of 8 channels (two a lane of a wavefront),
 the 512 heads that one pass of d dt holds); rows that do
 not fill a chunk of 16.  Against the float64 oracles, at the bounds of
 test_gpu_block and test_gpu_block_backward."""
+import numpy as np
 import pytest
 
 import oracle.block as ob
@@ -59,3 +60,35 @@ def test_row_counts(rows, H, P, G, group, gate, weight, dtype):
     for k in ("dx", "dA_log", "dB", "dC", "ddt_bias") + (("dz",) if gate else ()) + (("dnorm_weight",) if weight else ()):
         check(k, got[k], ref[k], TOL[dtype])
     check("ddt_raw", got["ddt"], ref["ddt_raw"], TOL[dtype])
+
+
+@pytest.mark.parametrize("heads", [33, 80])
+def test_gate_is_exact_to_float32(heads):
+    """The gate's SiLU, seen through a rounding of the result to bf16: y is x (B =
+    C = 0, D = 1), gated by z and normalised over the row, and each channel's
+    weight puts the exact result 1e-6 of its value above or below the middle of
+    two bf16 values.  Float32's errors (SiLU 2e-7, the weight and three products
+    2^-24 each, the root 2^-23, and none in the mean square, which is far below
+    eps) add up to 6e-7: every channel has to land on its side."""
+    import torch
+    from paper_2405_21060_amd import ssd
+    from paper_2405_21060_amd.inputs import bf16_bits_to_f32, f32_to_bf16_bits
+
+    announce("gate to float32, %d heads" % heads)
+    rng = np.random.default_rng(45)
+    n = heads * 64
+    z = np.concatenate([rng.uniform(-85.0, -20.0, n - n // 8), rng.uniform(-88.5, -85.0, n // 8)])
+    z = bf16_bits_to_f32(f32_to_bf16_bits(rng.permutation(z).astype(np.float32))).astype(np.float64)
+    x = rng.choice([-1.0, -2.0, 0.5, 4.0], n)
+    k, side = rng.integers(0, 127, n), rng.choice([-1, 1], n)
+    mid = 1.0 + (2 * k + 1) / 256.0
+    g = x * z / (1.0 + np.exp(-z))
+    w = (mid * (1.0 + 1e-6 * side) / (g / np.sqrt((g * g).mean() + 1e-5))).astype(np.float32)
+    dev = lambda a, *s: torch.from_numpy(a).cuda().to(torch.bfloat16).view(1, 1, *s)
+    zero = torch.zeros((1, 1, 1, 64), dtype=torch.bfloat16, device="cuda")
+    one = torch.ones(heads, device="cuda")
+    y, _ = ssd.forward_block(dev(x, heads, 64), torch.zeros((1, 1, heads), dtype=torch.bfloat16, device="cuda"), one,
+                             zero, zero, one, z=dev(z, heads, 64), norm_weight=torch.from_numpy(w).cuda(),
+                             norm_group_size=n)
+    wrong = np.flatnonzero(to_f64(y).reshape(-1) != mid + side / 256.0)
+    assert wrong.size == 0, (wrong.size, z[wrong[:8]], to_f64(y).reshape(-1)[wrong[:8]], mid[wrong[:8]], side[wrong[:8]])
