@@ -665,8 +665,8 @@ __global__ __launch_bounds__(kT2) void k_bwd2_chunk(BwdParams p, const float* __
             const float csend = lane_value(cs, L - 1);
             scs[lane] = cs;
             sdt[lane] = dtv;
-            seend[lane] = lane < L ? __builtin_amdgcn_exp2f(csend - cs) : 0.f;
-            secs[lane] = lane < L ? __builtin_amdgcn_exp2f(cs) : 0.f;
+            seend[lane] = lane < L ? exp2f(csend - cs) : 0.f;
+            secs[lane] = lane < L ? exp2f(cs) : 0.f;
         }
     };
     const auto store_gn = [&](int g2) {   // from the registers of fetch_gn
@@ -702,7 +702,7 @@ __global__ __launch_bounds__(kT2) void k_bwd2_chunk(BwdParams p, const float* __
 #pragma unroll
                 for (int v = 0; v < 4; ++v) {
                     const bool on = u0 + v >= t && u0 + v < L;
-                    const float e = __builtin_amdgcn_exp2f(cu[v] - cst);
+                    const float e = exp2f(cu[v] - cst);
                     const float r0 = acc[v] * dtt;
                     gs[v] = on ? e * g0[k][v] : 0.f;   // (not 0 times what may be infinite)
                     rs[v] = on ? e * r0 : 0.f;

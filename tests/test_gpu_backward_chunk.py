@@ -50,3 +50,30 @@ def test_later_tokens_do_not_see_an_infinite_score(N):
                               initial_states=d["initial_states"], dfinal_states=torch.from_numpy(dfinal).cuda()))
     for k in ("dx", "ddt"):
         assert torch.equal(g[0][k][:, 19:], g[1][k][:, 19:]), k
+
+
+@pytest.mark.parametrize("N", [64, 128])
+def test_decays_below_the_normal_range(N):
+    """A decay of 2^-130 is a float32 value (19 bits of it) and counts as one: a
+    state of 1e30 decayed by it gives dC of order 1e-9.  dC_0 = exp(dt A) h^T dy_0
+    with x = 0, each element a sum over 64 features of products of bf16 values
+    (the state is one), rounded to bf16."""
+    import torch
+    from paper_2405_21060_amd import ssd
+
+    announce("backward N %d, decay 2^-130" % N)
+    gen = torch.Generator().manual_seed(39)
+    bf = lambda *s: torch.randn(s, generator=gen).bfloat16()
+    H = 2
+    x, B, C = torch.zeros(1, 1, H, 64).bfloat16(), bf(1, 1, 1, N), bf(1, 1, 1, N)
+    dt, A_log = torch.ones(1, 1, H).bfloat16(), torch.full((H,), 90.1).log()
+    dy, init = bf(1, 1, H, 64), (torch.randn((1, H, 64, N), generator=gen) * 1e30).bfloat16().float()
+    g = ssd.backward(*(t.cuda() for t in (x, dt, A_log, B, C, dy)), initial_states=init.cuda())
+    decay = torch.exp(-A_log.double().exp())
+    terms = decay[:, None, None] * dy[0, 0].double()[:, :, None] * init[0].double()
+    ref = terms.sum((0, 1))
+    # half a bf16 unit of the value, and float32's exponent (2^-24 of 130, over
+    # log2 e) and the decay's own rounding (2^-20) on the terms' sum
+    bound = 2.0 ** -8 * ref.abs() + 2.0 ** -16 * terms.abs().sum((0, 1))
+    assert ref.abs().min() > 0
+    assert bool(((g["dC"].cpu().double()[0, 0, 0] - ref).abs() <= bound).all())
