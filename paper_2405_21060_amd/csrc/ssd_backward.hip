@@ -43,6 +43,9 @@
 // rows 4 q .. 4 q + 3) is the operand of the next product as it is.  64-wide
 // rows in shared memory are 68 floats apart: 16-byte reads of 16 rows, and
 // 4-byte reads of rows 4 q + v, both fall in different banks.
+// A diagonal score tile (u-tile = t-tile) holds pairs with u < t, whose scores are
+// zero.  Zero times an infinity is NaN, so where an operand of the chunk is not
+// finite, the products over that tile run pair by pair on the vector unit.
 #include "ssd_bwd.h"
 #include "ssd_device.h"
 
@@ -78,6 +81,15 @@ __device__ __forceinline__ float block_sum256(float v, float* scr)
     __syncthreads();
     return s;
 }
+
+// Zero if v is finite, else NaN; added up over a thread's values and over the
+// wavefront: whether all of them are.
+__device__ __forceinline__ float unless_finite(f32x4_t v)
+{
+    return fmaf(v[0], 0.f, fmaf(v[1], 0.f, fmaf(v[2], 0.f, v[3] * 0.f)));
+}
+
+__device__ __forceinline__ int any_not_finite(float z) { return __any(z != 0.f); }
 
 // Double through DPP and readlane, half by half.
 template <int CTRL, int ROWS>
@@ -301,6 +313,7 @@ __global__ __launch_bounds__(kBcThreads) void k_bwd_bc(BwdParams p, int split)
     __shared__ __attribute__((aligned(16))) float Rs[kQ * kLd];    // Rs  (row u, columns t <= u)
     __shared__ double scs[kQ];
     __shared__ float sdt[kQ], seend[kQ], secs[kQ], q1s[kQ][4], scr[8];
+    __shared__ int sbad[2][8];           // B, C not finite, by wavefront
     const int nb_all = tiles64(p.N);
     const int64_t c = blockIdx.x / split, b = blockIdx.y;
     const int64_t hpg = p.H / p.G, g = blockIdx.z / p.S, slice = blockIdx.z - g * p.S;
@@ -321,6 +334,8 @@ __global__ __launch_bounds__(kBcThreads) void k_bwd_bc(BwdParams p, int split)
         const T* Bp = static_cast<const T*>(p.B) + (t0 * p.G + g) * p.N + n0 + col;
         const T* Cp = static_cast<const T*>(p.C) + (t0 * p.G + g) * p.N + n0 + col;
         __syncthreads();   // (a second column block: the first one's reads are done)
+        float zb = 0.f, zc = 0.f;
+        int bad_b = 0, bad_c = 0;
 #pragma unroll
         for (int k = 0; k < kPer; ++k) {
             const int s = row0 + 32 * k;
@@ -331,6 +346,13 @@ __global__ __launch_bounds__(kBcThreads) void k_bwd_bc(BwdParams p, int split)
             }
             *reinterpret_cast<f32x4_t*>(&Bs[s * kLd + col]) = vb;
             *reinterpret_cast<f32x4_t*>(&Cs[s * kLd + col]) = vc;
+            zb += unless_finite(vb);
+            zc += unless_finite(vc);
+        }
+        const int nzb = any_not_finite(zb), nzc = any_not_finite(zc);
+        if (lane == 0) {
+            sbad[0][w] = nzb;
+            sbad[1][w] = nzc;
         }
         f32x4_t dB[2], dC[2];
 #pragma unroll
@@ -441,6 +463,15 @@ __global__ __launch_bounds__(kBcThreads) void k_bwd_bc(BwdParams p, int split)
                 }
             gh = wave_sum(gh);
             if (lane == 0) scr[w] = gh;
+            if (h == h_lo) {   // (stored before the barriers of this head's blocks)
+#pragma unroll
+                for (int k = 0; k < 8; ++k) {
+                    bad_b |= sbad[0][k];
+                    bad_c |= sbad[1][k];
+                }
+                bad_b = __builtin_amdgcn_readfirstlane(bad_b);
+                bad_c = __builtin_amdgcn_readfirstlane(bad_c);
+            }
             __syncthreads();
             if (cols) {
 #pragma unroll
@@ -448,7 +479,7 @@ __global__ __launch_bounds__(kBcThreads) void k_bwd_bc(BwdParams p, int split)
                     const int tt = tp + j, t = 16 * tt + r;
                     // dB^T(n, t) += sum over u >= t of C^T Rs
 #pragma unroll 1
-                    for (int uj = tt; uj < kQ / 16; ++uj)
+                    for (int uj = tt + bad_c; uj < kQ / 16; ++uj)
 #pragma unroll
                         for (int v = 0; v < 4; ++v) {
                             const int u = 16 * uj + 4 * q + v;
@@ -456,7 +487,7 @@ __global__ __launch_bounds__(kBcThreads) void k_bwd_bc(BwdParams p, int split)
                         }
                     // dC^T(n, u = t) += sum over s <= u of B^T Rs^T
 #pragma unroll 1
-                    for (int sj = 0; sj <= tt; ++sj) {
+                    for (int sj = 0; sj + bad_b <= tt; ++sj) {
                         const f32x4_t rv = *reinterpret_cast<const f32x4_t*>(&Rs[t * kLd + 16 * sj + 4 * q]);
 #pragma unroll
                         for (int v = 0; v < 4; ++v)
@@ -467,6 +498,20 @@ __global__ __launch_bounds__(kBcThreads) void k_bwd_bc(BwdParams p, int split)
                     float q1 = 0.f;
                     settle(dB[j]);
                     settle(dC[j]);
+                    if (bad_c) {   // the diagonal tile, pair by pair
+#pragma unroll 1
+                        for (int u = 16 * tt; u < 16 * tt + 16; ++u)
+#pragma unroll
+                            for (int v = 0; v < 4; ++v)
+                                if (u >= t) dB[j][v] = fmaf(Cs[u * kLd + 16 * nt + 4 * q + v], Rs[u * kLd + t], dB[j][v]);
+                    }
+                    if (bad_b) {
+#pragma unroll 1
+                        for (int s1 = 16 * tt; s1 < 16 * tt + 16; ++s1)
+#pragma unroll
+                            for (int v = 0; v < 4; ++v)
+                                if (s1 <= t) dC[j][v] = fmaf(Bs[s1 * kLd + 16 * nt + 4 * q + v], Rs[t * kLd + s1], dC[j][v]);
+                    }
 #pragma unroll
                     for (int v = 0; v < 4; ++v) {
                         dB[j][v] = fmaf(fb, bx[j][v], dB[j][v]);
@@ -522,6 +567,7 @@ __global__ __launch_bounds__(kThreads) void k_bwd_dx(BwdParams p)
     __shared__ __attribute__((aligned(16))) float Gs[P * kLd];
     __shared__ double scs[kQ];
     __shared__ float sdt[kQ], seend[kQ], secs[kQ], xdx[kQ], q2s[kQ], dyxs[kQ], cols[kQ], rowp[kQ][4], scr[4];
+    __shared__ int sbad[4];              // dy not finite, by wavefront
     const int64_t c = blockIdx.x, b = blockIdx.y, h = blockIdx.z, g = h / (p.H / p.G), bh = b * p.H + h;
     const int tid = threadIdx.x, lane = tid & 63, r = lane & 15, q = lane >> 4;
     const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -557,8 +603,14 @@ __global__ __launch_bounds__(kThreads) void k_bwd_dx(BwdParams p)
             *reinterpret_cast<f32x4_t*>(&xs[s * XS + f]) = vx[k];
             *reinterpret_cast<f32x4_t*>(&dys[s * XS + f]) = vd[k];
         }
+        float z = 0.f;
+#pragma unroll
+        for (int k = 0; k < kPer; ++k) z += unless_finite(vd[k]);
+        const int nz = any_not_finite(z);
+        if (lane == 0) sbad[wv] = nz;
     }
     __syncthreads();
+    const int bad = __builtin_amdgcn_readfirstlane(sbad[0] | sbad[1] | sbad[2] | sbad[3]);
 
     // scores on the tiles u >= t of this t-tile: Gs into dy^T Gs, l into its row and column sums
     f32x4_t ai[PT], ag[PT];
@@ -598,6 +650,21 @@ __global__ __launch_bounds__(kThreads) void k_bwd_dx(BwdParams p)
             colsum += lv;
             const float rsum = row_sum16(lv);
             if (r == 0) rowp[u][w] = rsum;
+        }
+        if (bad && uj == w) {   // the diagonal tile (this wavefront's first), pair by pair
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+#pragma unroll 1
+                for (int k = 0; k < 4; ++k) {
+                    const int u = 16 * uj + 4 * k + v;
+                    const float gut = __shfl(gs[v], 16 * k + r, 64);
+#pragma unroll
+                    for (int pt = 0; pt < PT; ++pt)
+#pragma unroll
+                        for (int e = 0; e < 4; ++e)
+                            if (u >= t) ai[pt][e] = fmaf(dys[u * XS + 16 * pt + 4 * q + e], gut, ai[pt][e]);
+                }
+            continue;
         }
 #pragma unroll
         for (int v = 0; v < 4; ++v)

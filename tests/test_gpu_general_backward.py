@@ -46,3 +46,36 @@ def test_decay_that_vanishes(tune):
     got, ref = gpu_backward(inp, dy, dfinal, True, True), oracle_backward(inp, dy, dfinal, True, True)
     for k in ("dx", "ddt", "dB", "dC", "dA_log", "dD", "dinit"):
         check(k, got[k], ref[k], 2e-5)
+
+
+@pytest.mark.parametrize("shape", [(64, 128, 1, "f32"), (80, 144, 2, "f32"), (128, 64, 1, "bf16"), (16, 16, 1, "f32")], ids=str)
+@pytest.mark.parametrize("name,token", [("dy", 18), ("dy", 70), ("C", 18), ("C", 64), ("B", 27), ("B", 95)])
+def test_an_infinite_operand_stays_with_its_pairs(shape, name, token):
+    """One token's dy, C or B infinite: the gradients whose sums leave that token
+    out are what they are without it -- dx and ddt of later tokens for dy, dB of
+    later tokens for C, dC of earlier ones for B -- although its score tile holds
+    their (zero) scores too.  (Up to the order of a tile's float32 sum: 2^-24
+    times its sixteen terms, relative to the largest gradient.)"""
+    import numpy as np
+    import torch
+    from paper_2405_21060_amd import ssd
+    from tests.ssd_harness import act_to_device, to_device, to_f64
+
+    P, N, G, dtype = shape
+    announce("general backward P%d N%d %s, %s of token %d infinite" % (P, N, dtype, name, token))
+    inp = make_inputs(Problem(1, 100, 4, P, N, G, 256, dtype, init_states=True), 33)
+    dy, dfinal = make_grad_inputs(inp.problem, 33)
+    d = to_device(inp)
+    d["dy"] = act_to_device(dy)
+    g = []
+    for bad in (False, True):
+        t = {k: d[k].clone() for k in ("dy", "C", "B")}
+        if bad:
+            t[name][0, token] = float("inf")
+        g.append(ssd.backward(d["x"], d["dt"], d["A_log"], t["B"], t["C"], t["dy"], D=d["D"],
+                              initial_states=d["initial_states"], dfinal_states=torch.from_numpy(dfinal).cuda()))
+    far = slice(0, token) if name == "B" else slice(token + 1, None)
+    for k in {"dy": ("dx", "ddt"), "C": ("dB",), "B": ("dC",)}[name]:
+        a, b = to_f64(g[0][k])[:, far], to_f64(g[1][k])[:, far]
+        assert np.all(np.isfinite(b)), k
+        assert np.abs(a - b).max() <= (2.0 ** -20 if dtype == "f32" else 2.0 ** -8) * np.abs(a).max(), k
