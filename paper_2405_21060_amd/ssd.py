@@ -263,6 +263,22 @@ def _workspace(workspace, need: int, dev):
     return workspace
 
 
+def _forward_workspace(workspace, need: int, dev):
+    """The workspace of a forward, and its size: a new one of ``need`` bytes, or
+    the caller's, of which the call itself says whether it is enough (the least
+    it runs on can be below what it runs best on, which ``need`` is)."""
+    if workspace is None:
+        return _workspace(None, need, dev), need
+    return workspace, workspace.numel() * workspace.element_size()
+
+
+def _check_forward(rc: int, where: str, workspace, size: int, need: int) -> None:
+    if rc == SSD_ERR_WORKSPACE and workspace is not None:
+        raise ValueError("workspace holds %d bytes, the call needs %d" % (size, need))
+    if rc != SSD_OK:
+        raise SsdError(rc, where)
+
+
 def ssd_forward_block(prob: SsdProblem, opts: SsdBlockOpts, x, dt, A_log, B, C, D, initial_states,
                       seq_idx, y, final_states, workspace, workspace_bytes: int, stream) -> int:
     """Raw ABI call on integer device addresses (0 = NULL); returns the status."""
@@ -322,8 +338,8 @@ def _call(opts, x, dt, A_log, B, C, D, chunk_size, initial_states, seq_idx, nseq
     if seq_idx is not None and nseq is None:
         nseq = int(seq_idx[0, -1].item()) + 1
     prob = make_problem(b, T, H, P, N, G, chunk_size, dtype, nseq or 0)
-    wsb = ssd_workspace_bytes(prob)
-    workspace = _workspace(workspace, wsb, dev)
+    need = ssd_workspace_bytes(prob)
+    ws, wsb = _forward_workspace(workspace, need, dev)
     y = out if out is not None else torch.empty_like(x)
     units = nseq if seq_idx is not None else b
     fin = None
@@ -332,13 +348,12 @@ def _call(opts, x, dt, A_log, B, C, D, chunk_size, initial_states, seq_idx, nseq
             (units, H, P, N), dtype=torch.float32, device=dev)
     stream = torch.cuda.current_stream(dev).cuda_stream
     args = (_ptr(x), _ptr(dt), _ptr(A_log), _ptr(B), _ptr(C), _ptr(D), _ptr(initial_states),
-            _ptr(seq_idx), _ptr(y), _ptr(fin), _ptr(workspace), wsb, stream)
+            _ptr(seq_idx), _ptr(y), _ptr(fin), _ptr(ws), wsb, stream)
     if opts is None:
         rc, where = ssd_forward(prob, *args), "ssd_forward"
     else:
         rc, where = ssd_forward_block(prob, opts, *args), "ssd_forward_block"
-    if rc != SSD_OK:
-        raise SsdError(rc, where)
+    _check_forward(rc, where, workspace, wsb, need)
     return y, fin
 
 
@@ -725,13 +740,12 @@ def forward_varlen(x, dt, A_log, B, C, seq_starts, D=None, chunk_size: int = 256
     nseq = len(seq_starts) - 1
     prob = make_problem(1, T, H, P, N, G, chunk_size,
                         SSD_DTYPE_BF16 if x.dtype == torch.bfloat16 else SSD_DTYPE_F32, nseq)
-    wsb = ssd_forward_varlen_workspace_bytes(prob, seq_starts)
-    workspace = _workspace(workspace, wsb, dev)
+    need = ssd_forward_varlen_workspace_bytes(prob, seq_starts)
+    ws, wsb = _forward_workspace(workspace, need, dev)
     y = out if out is not None else torch.empty_like(x)
     fin = torch.empty((nseq, H, P, N), dtype=torch.float32, device=dev) if return_final_states else None
     rc = ssd_forward_varlen(prob, seq_starts, _ptr(x), _ptr(dt), _ptr(A_log), _ptr(B), _ptr(C), _ptr(D),
-                            _ptr(initial_states), _ptr(y), _ptr(fin), _ptr(workspace), wsb,
+                            _ptr(initial_states), _ptr(y), _ptr(fin), _ptr(ws), wsb,
                             torch.cuda.current_stream(dev).cuda_stream)
-    if rc != SSD_OK:
-        raise SsdError(rc, "ssd_forward_varlen")
+    _check_forward(rc, "ssd_forward_varlen", workspace, wsb, need)
     return y, fin

@@ -181,3 +181,33 @@ def test_final_states_round_the_weighted_x(P, N):
     xw = bf16_bits_to_f32(f32_to_bf16_bits(xw)).astype(np.float64)
     ref = np.matmul(xw.transpose(0, 2, 3, 1), B[:, :, 0][:, None])
     assert np.linalg.norm(to_f64(fin) - ref) <= 4 * 2.0 ** -14 * np.linalg.norm(ref)
+
+
+@pytest.mark.parametrize("host", [False, True])
+def test_python_callers_workspace_of_the_general_size(tune, host):
+    """``forward`` and ``forward_varlen`` hand a caller's workspace on as it is:
+    the general kernels' size is enough, one byte less is refused."""
+    import torch
+    from paper_2405_21060_amd import ssd
+
+    announce("general kernels on a Python caller's workspace, host offsets %s" % host)
+    inp = _inputs(1, 64, 8, 128, 128, 1, 32, seed=21, varlen=True, len_lo=32, len_hi=32)
+    d, starts = to_device(inp), [0, 32, 64]
+    p = ssd.make_problem(1, 64, 8, 128, 128, 1, 32, ssd.SSD_DTYPE_BF16, 2)
+    size = lambda: ssd.ssd_forward_varlen_workspace_bytes(p, starts) if host else ssd.ssd_workspace_bytes(p)
+    best = size()
+    tune("force_general_path", 1)
+    general = size()
+    tune("force_general_path", 0)
+    assert general < best
+
+    def call(ws):
+        args = (d["x"], d["dt"], d["A_log"], d["B"], d["C"])
+        kw = dict(chunk_size=32, initial_states=d["initial_states"], workspace=ws)
+        if host:
+            return ssd.forward_varlen(*args, starts, d["D"], **kw)
+        return ssd.forward(*args, d["D"], seq_idx=d["seq_idx"], nseq=2, **kw)
+
+    compare(inp, *call(torch.empty(general, dtype=torch.uint8, device="cuda")))
+    with pytest.raises(ValueError):
+        call(torch.empty(general - 1, dtype=torch.uint8, device="cuda"))
