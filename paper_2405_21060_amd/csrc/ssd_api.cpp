@@ -173,7 +173,10 @@ ssd::FusedLayout fused_plan(const ssd::Shape& s, int64_t nseq)
 
 bool fused_shape(const ssd::Shape& s)
 {
-    return ssd::tuning(ssd::kTuneForceGeneral) != 1 && ssd::fused_supported(s.H, s.P, s.N, s.bf16);
+    // (batch rows x groups are on grid y of their first kernel; the general
+    // kernels, which have the two on grid y and z, keep the calls beyond it)
+    return ssd::tuning(ssd::kTuneForceGeneral) != 1 && ssd::fused_supported(s.H, s.P, s.N, s.bf16) &&
+           (fused_own(s) || s.b * s.G <= 65535);
 }
 
 // The fused kernels' own shape: always theirs.  Their other shapes fall back to

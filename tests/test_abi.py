@@ -325,3 +325,18 @@ def test_tuning_context_leaves_nothing_set_on_a_refused_setting(lib):
 def test_workspace_status_null(lib):
     assert ssd.ssd_workspace_status(0, 0) == ssd.SSD_ERR_NULL_ARG
     assert "state" in ssd.ssd_error_string(ssd.SSD_ERR_STATE_TIMEOUT)
+
+
+@pytest.mark.parametrize("headdim,chunk", [(128, 32), (64, 32)])
+def test_more_rows_than_the_fused_grid(lib, headdim, chunk):
+    """Headdim 128 and short chunks: beyond 65,535 batch rows x groups (grid y of
+    the fused kernels' first one) the call is the general kernels', as its
+    workspace says; up to there it covers the fused ones too."""
+    def size(batch):
+        return ssd.ssd_workspace_bytes(prob(batch=batch, seqlen=1, nheads=2, ngroups=2, headdim=headdim, dstate=64,
+                                            chunk_size=chunk))
+
+    both = size(32767), size(33000)
+    with ssd.tuning(force_general_path=1):
+        general = size(32767), size(33000)
+    assert both[0] > general[0] and both[1] == general[1]

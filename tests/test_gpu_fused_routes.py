@@ -211,3 +211,11 @@ def test_python_callers_workspace_of_the_general_size(tune, host):
     compare(inp, *call(torch.empty(general, dtype=torch.uint8, device="cuda")))
     with pytest.raises(ValueError):
         call(torch.empty(general - 1, dtype=torch.uint8, device="cuda"))
+
+
+def test_more_rows_than_the_fused_grid():
+    """66,000 batch rows x groups: past the fused kernels' grid, on the general ones."""
+    announce("general kernels, 33,000 rows of two groups")
+    inp = make_inputs(Problem(33000, 1, 2, 128, 64, 2, 32, "bf16"), 22)
+    y, _ = run_gpu(inp, final=False)
+    compare(inp, y, None)
