@@ -904,9 +904,6 @@ BwdLayout bwd_layout(int64_t b, int64_t T, int64_t H, int64_t P, int64_t N, int6
         l.gram = take(static_cast<size_t>(b * G * nC * kBwdQ * kBwdQ));
         l.q1p = take(static_cast<size_t>(nblk * b * H * T));
         l.ghp = take(static_cast<size_t>(nblk * b * H * nC));
-        // the size stays that of two float32 states per 32 tokens, which callers size for
-        const size_t states32 = static_cast<size_t>(b * ((T + 31) / 32) * H * P * N) * 8;
-        if (off < states32) off = al(states32);
     }
     l.dBp = take(static_cast<size_t>(S * b * T * G * N));
     l.dCp = take(static_cast<size_t>(S * b * T * G * N));
