@@ -323,13 +323,19 @@ def test_deterministic_repeat():
     assert torch.equal(f1, f2)
 
 
-def test_chunk_size_independence_large():
+def test_chunk_size_independence_large(tune):
     """Chunk-size independence at a size beyond the oracle's comfort: the
-    block decomposition is exact for any block length (Section 6)."""
+    block decomposition is exact for any block length (Section 6).  The fused
+    kernels work in chunks of 256 whatever the call says, the general ones in
+    the call's."""
     inp = make_inputs(Problem(2, 4096, 16, 64, 128, 1, 256, "bf16"), 4)
     ys = [to_f64(run_gpu(inp, chunk_size=Q)[0]) for Q in (64, 128, 256)]
-    for y in ys[:-1]:
+    tune("force_general_path", 1)
+    general = [to_f64(run_gpu(inp, chunk_size=Q)[0]) for Q in (32, 64, 128, 256)]
+    for y in ys[:-1] + general:
         assert rel_err(y, ys[-1]) <= TOL["bf16"]
+    for y in general[:-1]:   # another decomposition each: other roundings
+        assert not np.array_equal(y, general[-1])
 
 
 # Full-size workloads: every configuration of the benchmark's workload list
