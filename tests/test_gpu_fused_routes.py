@@ -2,7 +2,8 @@
 (two of their heads a head) and block lengths other than their own, plain and
 packed rows, with the block steps -- and the calls of those shapes that stay on
 the general kernels (operands off 16 bytes, a workspace of the general size).
-Against the float64 oracle, at the bounds of test_gpu_parity.
+Against the float64 oracle, at the bounds of test_gpu_parity, and, for which
+kernels ran, against the forced general path bit for bit.
 """
 import numpy as np
 import pytest
@@ -32,11 +33,24 @@ def _inputs(b, T, H, P, N, G, Q, seed, **kw):
     return make_inputs(Problem(b, T, H, P, N, G, Q, "bf16", init_states=True, **kw), seed)
 
 
+def _same_as_general(tune, outputs, call):
+    """Whether `outputs` are bit for bit the general kernels' (the two sum in
+    different orders, so that only the same kernels give the same bits)."""
+    import torch
+
+    tune("force_general_path", 1)
+    general = call()
+    tune("force_general_path", 0)
+    return all(torch.equal(a, b) for a, b in zip(outputs, general))
+
+
 @pytest.mark.parametrize("shape", PLAIN)
-def test_plain_rows(shape):
+def test_plain_rows(shape, tune):
     announce("fused route %s" % (shape,))
     inp = _inputs(*shape, seed=11)
-    compare(inp, *run_gpu(inp))
+    y, fin = run_gpu(inp)
+    compare(inp, y, fin)
+    assert not _same_as_general(tune, (y, fin), lambda: run_gpu(inp))
     y, fin = run_gpu(inp, use_D=False, use_init=False)
     inp.D, inp.initial_states = np.zeros_like(inp.D), None
     compare(inp, y, fin)
@@ -44,18 +58,23 @@ def test_plain_rows(shape):
 
 @pytest.mark.parametrize("P,N,G,Q", [(128, 128, 1, 256), (128, 64, 2, 64), (64, 128, 2, 128)])
 @pytest.mark.parametrize("host", [False, True])
-def test_packed_rows(P, N, G, Q, host):
+def test_packed_rows(P, N, G, Q, host, tune):
     from paper_2405_21060_amd import ssd
 
     announce("fused route, packed P%d N%d G%d Q%d host %s" % (P, N, G, Q, host))
     inp = _inputs(1, 1500, 4, P, N, G, Q, seed=12, varlen=True, len_lo=1, len_hi=600)
     if not host:
-        compare(inp, *run_gpu(inp))
+        y, fin = run_gpu(inp)
+        compare(inp, y, fin)
+        assert not _same_as_general(tune, (y, fin), lambda: run_gpu(inp))
         return
     d = to_device(inp)
     starts = [0] + [int(v) + 1 for v in np.flatnonzero(np.diff(inp.seq_idx[0]))] + [1500]
-    compare(inp, *ssd.forward_varlen(d["x"], d["dt"], d["A_log"], d["B"], d["C"], starts, d["D"], chunk_size=Q,
-                                     initial_states=d["initial_states"]))
+    call = lambda: ssd.forward_varlen(d["x"], d["dt"], d["A_log"], d["B"], d["C"], starts, d["D"], chunk_size=Q,
+                                      initial_states=d["initial_states"])
+    y, fin = call()
+    compare(inp, y, fin)
+    assert not _same_as_general(tune, (y, fin), call)
 
 
 @pytest.mark.parametrize("P,Q", [(128, 256), (64, 64)])
@@ -63,19 +82,15 @@ def test_packed_rows(P, N, G, Q, host):
 def test_short_packed_sequences_stay_general(tune, P, Q, length, general):
     """A chunk per sequence costs the fused kernels 256 tokens' work: rows of
     sequences shorter than 24 tokens on average run on the general kernels."""
-    import torch
-
     announce("packed, sequences of %d, P%d Q%d" % (length, P, Q))
     inp = _inputs(1, 500, 3, P, 128, 1, Q, seed=20, varlen=True, len_lo=length, len_hi=length)
     y, fin = run_gpu(inp)
     compare(inp, y, fin)
-    tune("force_general_path", 1)
-    y2, fin2 = run_gpu(inp)
-    assert (torch.equal(y, y2) and torch.equal(fin, fin2)) == general
+    assert _same_as_general(tune, (y, fin), lambda: run_gpu(inp)) == general
 
 
 @pytest.mark.parametrize("group", [0, 128, 512])
-def test_block_headdim_128(group):
+def test_block_headdim_128(group, tune):
     announce("fused route, block P128 norm group %d" % group)
     bi = make_block_inputs(Problem(2, 400, 4, 128, 128, 2, 128, "bf16"), 13)
     opts = dict(norm_group_size=group)
@@ -83,10 +98,11 @@ def test_block_headdim_128(group):
     y_ref, fin_ref = ob.block_forward_inputs(bi, opts)
     assert rel_err(to_f64(y), y_ref) <= TOL["bf16"]
     assert rel_err(to_f64(fin), fin_ref) <= TOL["bf16"]
+    assert not _same_as_general(tune, (y, fin), lambda: run_block(bi, opts))
 
 
 @pytest.mark.parametrize("what", ["x", "B", "C", "y"])
-def test_operand_off_16_bytes_stays_general(what):
+def test_operand_off_16_bytes_stays_general(what, tune):
     """An activation one element off: the general kernels' result, as before."""
     import torch
     from paper_2405_21060_amd import ssd
@@ -104,8 +120,12 @@ def test_operand_off_16_bytes_stays_general(what):
         out = off(out)
     else:
         d[what] = off(d[what])
-    compare(inp, *ssd.forward(d["x"], d["dt"], d["A_log"], d["B"], d["C"], d["D"], chunk_size=128,
-                              initial_states=d["initial_states"], out=out))
+    call = lambda: ssd.forward(d["x"], d["dt"], d["A_log"], d["B"], d["C"], d["D"], chunk_size=128,
+                               initial_states=d["initial_states"], out=out)
+    y, fin = call()
+    compare(inp, y, fin)
+    y = y.clone()
+    assert _same_as_general(tune, (y, fin), call)
 
 
 def test_workspace_of_the_general_size_is_enough(tune):
@@ -131,6 +151,7 @@ def test_workspace_of_the_general_size_is_enough(tune):
         assert rc == want
     torch.cuda.synchronize()
     compare(inp, y, fin)
+    assert _same_as_general(tune, (y, fin), lambda: run_gpu(inp))
 
 
 @pytest.mark.parametrize("P,Q,N,packed", [(128, 256, 128, False), (128, 64, 64, True), (64, 128, 128, False),
