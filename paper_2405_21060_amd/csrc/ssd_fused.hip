@@ -367,23 +367,25 @@ __global__ __launch_bounds__(kTabThreads) void k_seq_order(const int4* __restric
     for (int e = threadIdx.x; e < n; e += kTabThreads) vorder[atomicAdd(&pos[depth(e)], 1)] = e;
 }
 
-// One Gram tile's four values of a lane to its place: rounded to bf16, or, with
-// gram_lo, in float32 as their upper halves there and their lower halves in
-// gram_lo.
-__device__ __forceinline__ void store_gram(const FusedParams& p, int64_t pos, f32x4_t v)
+// Four values of a Gram tile to their place: rounded to bf16, or (G32) in
+// float32, their upper halves there and their lower halves in `low`.
+template <bool G32>
+__device__ __forceinline__ void store_gram(u16* gram, u16* low, int64_t pos, f32x4_t v)
 {
     uint2 packed;
-    if (p.gram_lo) {
+    if constexpr (G32) {
         packed = make_uint2(upper16x2(v[0], v[1]), upper16x2(v[2], v[3]));
-        *reinterpret_cast<uint2*>(p.gram_lo + pos) = make_uint2(lower16x2(v[0], v[1]), lower16x2(v[2], v[3]));
+        *reinterpret_cast<uint2*>(low + pos) = make_uint2(lower16x2(v[0], v[1]), lower16x2(v[2], v[3]));
     } else {
-        packed = make_uint2(pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]));
+        packed.x = pack_bf16x2(v[0], v[1]);
+        packed.y = pack_bf16x2(v[2], v[3]);
     }
-    *reinterpret_cast<uint2*>(p.gram + pos) = packed;
+    *reinterpret_cast<uint2*>(gram + pos) = packed;
 }
 
-// PACKED: a packed row, chunk positions from the chunk table.
-template <int N, bool PACKED>
+// PACKED: a packed row, chunk positions from the chunk table.  (G32 as a run-time
+// branch cost the packed row's 72 us 13 %.)
+template <int N, bool PACKED, bool G32>
 __global__ __launch_bounds__(kPrepThreads) void k_fused_prep(FusedParams p)
 {
     constexpr int RS = N + 8;
@@ -414,7 +416,9 @@ __global__ __launch_bounds__(kPrepThreads) void k_fused_prep(FusedParams p)
         const int64_t brow = p.G * N;
         const u16* Bchunk = static_cast<const u16*>(p.B) + ((b * p.T + c0) * p.G + g) * N;
         const u16* Cchunk = static_cast<const u16*>(p.C) + ((b * p.T + c0) * p.G + g) * N;
-        const int64_t gram = ((static_cast<int64_t>(b) * p.G + g) * p.nC + c) * kTiles * 256;
+        const int64_t gram0 = ((static_cast<int64_t>(b) * p.G + g) * p.nC + c) * kTiles * 256;
+        u16* gram = p.gram + gram0;
+        u16* low = G32 ? p.gram_lo + gram0 : nullptr;
         u16* bt = p.BT + ((static_cast<int64_t>(b) * p.G + g) * p.nC + c) * N * kQ;
         for (int part = blockIdx.z; part < kGramParts; part += gridDim.z) {
             if (part != static_cast<int>(blockIdx.z)) __syncthreads();   // the previous part's LDS reads are done
@@ -488,7 +492,7 @@ __global__ __launch_bounds__(kPrepThreads) void k_fused_prep(FusedParams p)
 #pragma unroll
             for (int kk = 0; kk < kNQ / 2; ++kk) {
                 const int j = (wave & 1) + 2 * kk;
-                if (j <= i) store_gram(p, gram + (tile_index(i, j) * 64 + lane) * 4, acc[kk]);
+                if (j <= i) store_gram<G32>(gram, low, (static_cast<int64_t>(tile_index(i, j)) * 64 + lane) * 4, acc[kk]);
             }
         }
     } else {
@@ -545,7 +549,9 @@ __global__ __launch_bounds__(kPrepThreads) void k_fused_prep(FusedParams p)
 
         // ---- Gram tiles G^T[s][t] = sum_n B_s[n] C_t[n], accumulator layout per lane.
         // Wavefront w: row rows[w / 2], s-tiles j = w%2, w%2 + 2, ...
-        const int64_t gram = ((static_cast<int64_t>(b) * p.G + g) * p.nC + c) * kTiles * 256;
+        const int64_t gram0 = ((static_cast<int64_t>(b) * p.G + g) * p.nC + c) * kTiles * 256;
+        u16* gram = p.gram + gram0;
+        u16* low = G32 ? p.gram_lo + gram0 : nullptr;
         {
             const int i = rows[wave >> 1];
             uint4 cfr[N / 32];
@@ -560,7 +566,7 @@ __global__ __launch_bounds__(kPrepThreads) void k_fused_prep(FusedParams p)
                     const uint4 va = *reinterpret_cast<const uint4*>(&sm.B[(16 * j + r) * RS + 32 * k + 8 * lg]);
                     acc = mfma(as_bf16x8(va), as_bf16x8(cfr[k]), acc);
                 }
-                store_gram(p, gram + (tile_index(i, j) * 64 + lane) * 4, acc);
+                store_gram<G32>(gram, low, (static_cast<int64_t>(tile_index(i, j)) * 64 + lane) * 4, acc);
             }
         }
 
@@ -1726,10 +1732,11 @@ hipError_t launch_n(const FusedParams& p, hipStream_t stream, hipEvent_t ev_begi
     const int64_t pairs = p.nC * p.b * p.G;
     const unsigned gz = pairs * kGramParts <= 2 * cus ? kGramParts : (pairs * 2 <= 2 * cus ? 2 : 1);
     const dim3 g_prep(static_cast<unsigned>(p.nC), static_cast<unsigned>(p.b * p.G), gz);
-    if (p.vtab)
-        hipLaunchKernelGGL((k_fused_prep<N, true>), g_prep, dim3(kPrepThreads), 0, stream, p);
+    const auto prep = [&](auto kern) { hipLaunchKernelGGL(kern, g_prep, dim3(kPrepThreads), 0, stream, p); };
+    if (p.gram_lo)
+        p.vtab ? prep(k_fused_prep<N, true, true>) : prep(k_fused_prep<N, false, true>);
     else
-        hipLaunchKernelGGL((k_fused_prep<N, false>), g_prep, dim3(kPrepThreads), 0, stream, p);
+        p.vtab ? prep(k_fused_prep<N, true, false>) : prep(k_fused_prep<N, false, false>);
     err = hipGetLastError();
     if (err == hipSuccess && ev_begin) err = hipEventRecord(ev_begin, stream);
     if (err != hipSuccess) return err;

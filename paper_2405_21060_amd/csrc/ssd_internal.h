@@ -101,9 +101,6 @@ struct FusedParams {
     float* fin;
     // workspace
     uint16_t* gram;   // (b, G, nC, tiles, 64 lanes, 4) causal Gram tiles, bf16, per-lane layout
-    // not null: the Gram values are float32, gram holding the upper and gram_lo
-    // the lower 16 bits of each
-    uint16_t* gram_lo = nullptr;
     uint16_t* BT;     // (b, G, nC, N, Q) B^T per chunk, bf16
     float* ring;      // (b, H, 2, P, N) chunk-state ring
     int* flags;       // (b, H, nC)      state-published flags
@@ -142,8 +139,12 @@ struct FusedParams {
     // nonzero: y is float32 (plain rows, no gate or normalisation)
     int y32 = 0;
     // nonzero: headdim 128, each of the caller's heads two of these (dt, A_log,
-    // D and the dt bias have H / 2 heads)
+    // D and the dt bias have H / 2 heads); only with gram_lo
     int head128 = 0;
+    // not null: the Gram values are float32, gram holding the upper and gram_lo
+    // the lower 16 bits of each, and the weighted x is the rounded operand of the
+    // chunk states
+    uint16_t* gram_lo = nullptr;
 };
 
 struct FusedLayout {

@@ -240,3 +240,21 @@ def test_more_rows_than_the_fused_grid():
     inp = make_inputs(Problem(33000, 1, 2, 128, 64, 2, 32, "bf16"), 22)
     y, _ = run_gpu(inp, final=False)
     compare(inp, y, None)
+
+
+@pytest.mark.parametrize("early", [1, 2])
+@pytest.mark.parametrize("heads", [1, 2, 4])
+@pytest.mark.parametrize("P,N,packed", [(128, 64, False), (128, 128, True), (64, 256, False), (128, 256, True),
+                                        (64, 128, False)])
+def test_kernel_variants(tune, P, N, packed, heads, early):
+    """Late and early state flag, one and several heads an item, several items a
+    workgroup (their Gram tiles and operands fetched ahead)."""
+    announce("fused route P%d N%d packed %s, %d heads an item, flag %d" % (P, N, packed, heads, early))
+    tune("early_state_flag", early)
+    tune("heads_per_item", heads)
+    tune("max_workgroups", 3)
+    inp = _inputs(1 if packed else 2, 900, 4, P, N, 1, 256 if P == 128 else 64, seed=24,
+                  **(dict(varlen=True, len_lo=100, len_hi=600) if packed else {}))
+    y, fin = run_gpu(inp)
+    compare(inp, y, fin)
+    assert not _same_as_general(tune, (y, fin), lambda: run_gpu(inp))
