@@ -242,6 +242,33 @@ def test_more_rows_than_the_fused_grid():
     compare(inp, y, None)
 
 
+@pytest.mark.parametrize("P,Q", [(128, 256), (64, 128)])
+def test_decays_below_the_normal_range(P, Q):
+    """A decay of 2^-130 counts as one: with x of 1e30 at the first token, zero
+    elsewhere, and scores of 2^17 (their products with the decay are in the
+    normal range again), y of the tokens a step later is that operand, rounded to
+    bf16 once, times 1e30, rounded again: 2^-7 in all, and 2^-16 for the decay's
+    own 19 bits and float32's exponent."""
+    import torch
+    from paper_2405_21060_amd import ssd
+
+    announce("fused route, decay 2^-130, P%d Q%d" % (P, Q))
+    T, H, N = 40, 2, 128
+    gen = torch.Generator().manual_seed(23)
+    B = (32.0 * (1.0 + torch.rand((1, T, 1, N), generator=gen))).bfloat16()
+    C = (32.0 * (1.0 + torch.rand((1, T, 1, N), generator=gen))).bfloat16()
+    x = torch.zeros(1, T, H, P).bfloat16()
+    x[:, 0] = 1e30
+    dt = torch.zeros(1, T, H).bfloat16()
+    dt[:, 0], dt[:, 20] = 1.0, 1.0   # the decay falls between the tokens 19 and 20
+    A_log = torch.full((H,), 90.1).log()
+    y, _ = ssd.forward(x.cuda(), dt.cuda(), A_log.cuda(), B.cuda(), C.cuda(), chunk_size=Q)
+    decay = torch.exp(-A_log.double().exp())[None, :] ** (torch.arange(T) >= 20)[:, None]
+    ref = (C[0, :, 0].double() @ B[0, 0, 0].double())[:, None] * decay * x[0, 0, 0, 0].double()
+    err = ((y[0].cpu().double() - ref[..., None]).abs() / ref[..., None]).max()
+    assert err <= 2.0 ** -7 + 2.0 ** -16
+
+
 @pytest.mark.parametrize("early", [1, 2])
 @pytest.mark.parametrize("heads", [1, 2, 4])
 @pytest.mark.parametrize("P,N,packed", [(128, 64, False), (128, 128, True), (64, 256, False), (128, 256, True),
