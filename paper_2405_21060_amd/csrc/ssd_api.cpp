@@ -187,12 +187,13 @@ bool fused_only(const ssd::Shape& s) { return fused_shape(s) && fused_own(s); }
 
 // Where the fused kernels are the faster at their other shapes.  Plain rows:
 // everywhere (N 128, us against the general kernels': 8 heads of 128, one token
-// 21 / 30; 80 heads of 128, 64 rows of 64 tokens 355 / 2,045; 40 heads of 128, 2
-// x 4,096 tokens 132 / 607; headdim 64 with chunks of 64, 8 heads, 777 tokens 27 /
-// 35, 80 heads, 256 rows of 16 tokens 702 / 2,640).  A packed row costs a chunk
+// 21 / 30; 80 heads of 128, 64 rows of 64 tokens 369 / 2,045; 40 heads of 128, 2
+// x 4,096 tokens 134 / 607; headdim 64 with chunks of 64, 8 heads, 777 tokens 28 /
+// 35, 80 heads, 256 rows of 16 tokens 729 / 2,640).  A packed row costs a chunk
 // of 256 tokens' work per sequence: at 4,096 tokens, 24 heads of 128, sequences
-// of 16 tokens 485 / 452, of 24 347 / 433; of 64 with chunks of 64 262 / 201 and
-// 187 / 205.  (With host offsets the general kernels would run once a sequence.)
+// of 16 tokens 485 / 452, of 24 347 / 433, of 32 266 / 368; 24 heads of 64 with
+// chunks of 64 262 / 201, 187 / 205 and 160 / 168.  (With host offsets the general
+// kernels would run once a sequence.)
 bool fused_pays(const ssd::Shape& s, int64_t nseq) { return nseq == 0 || s.T >= 24 * nseq; }
 
 size_t general_bytes(const ssd::Shape& s)
@@ -342,6 +343,8 @@ int forward_impl(const ssd_problem* prob, const ssd_block_opts* opts, const void
         // 0.1908, the state-size sweep at N = 64 0.549 against 0.597, at N = 256
         // 1.256 against 1.295) and slower with items of 1-3 heads (130M layer,
         // the 8-way head and sequence splits: 2-4 %) and with the early flag.
+        // (Not with gram_lo: its right factor takes the weighted x, which is
+        // written over x after the diagonal block.)
         f.fuse_rf = !f.early_flag && f.HG >= 4 && !y32 ? 1 : 0;
         if (const int64_t fr = ssd::tuning(ssd::kTuneFusedRightFactor); fr == 1 || fr == 2)
             f.fuse_rf = fr == 2 && !f.early_flag && !y32;

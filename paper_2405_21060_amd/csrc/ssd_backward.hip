@@ -872,8 +872,8 @@ void bwd_slices(int64_t b, int64_t nC, int64_t G, int64_t hpg, int64_t* S, int64
 {
     // as few slices as still give every compute unit of the chip (256 CUs) a
     // workgroup: a workgroup shares B, C and the chunk's Gram tiles over its
-    // heads and accumulates dB, dC over them (measured at the 2.7B shape:
-    // 80 heads per workgroup 1.130 ms, 40: 1.139, 16: 1.165, 8: 1.217)
+    // heads and accumulates dB, dC over them (measured at the 2.7B shape, bf16:
+    // 80 heads per workgroup 0.610 ms, 40: 0.629, 16: 0.667, 8: 0.726)
     constexpr int64_t kCUs = 256;
     const int64_t units = b * nC * G;
     int64_t s = (kCUs + units - 1) / units;

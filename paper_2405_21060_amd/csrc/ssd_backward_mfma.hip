@@ -357,7 +357,8 @@ __global__ __launch_bounds__(kPassT, H32 ? 2 : 1) void k_bwd2_pass(BwdParams p)
 // issued at the head that uses them took 564 us at the 2.7B shape (4 x 4,096
 // tokens, 80 heads); reading one copy transposed 467, with the states fetched a
 // head ahead 403, and as a pipeline over the heads with one barrier a head
-// instead of three 364.  (128 registers, two workgroups per compute unit: 1,455
+// instead of three 364 (exp2f for the decays, which keeps those below 2^-126,
+// costs 6 of the whole backward's 602).  (128 registers, two workgroups per compute unit: 1,455
 // us, the operands fetched ahead are spilled.)
 template <int N>
 constexpr size_t chunk_smem()
@@ -805,7 +806,7 @@ __global__ __launch_bounds__(kT2) void k_bwd2_chunk(BwdParams p, const float* __
         const int r = o.r, q = o.q, p0 = 16 * pw + 4 * q;
         {
             float4 d32[2];
-            if constexpr (H32) {   // (just read by the fetch: from L2)
+            if constexpr (H32) {   // (read by the fetch three heads before, where it was rounded)
                 const __amdgpu_buffer_rsrc_t rd = __builtin_amdgcn_make_buffer_rsrc(
                     const_cast<float*>(static_cast<const float*>(p.dy)) + (t0 * p.H + h) * kP2, 0,
                     ((L - 1) * xrow + kP2) * 4, 0x00020000);

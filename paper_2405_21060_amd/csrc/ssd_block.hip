@@ -184,7 +184,7 @@ __global__ __launch_bounds__(kGateNormThreads) void k_gate_norm(GateNormParams p
 // workgroup of up to 512 threads per (row, group) and K (1 or 2) pieces per
 // thread, all loads of y and z in flight at once, one sum over the workgroup.
 // Memory-bound: reads y and z and writes y once.  At 16,384 rows of 5,120
-// channels, bf16, one group: 98 us for 503 MB, where one wavefront per group
+// channels, bf16, one group: 95 us for 503 MB, where one wavefront per group
 // (ten pieces a lane, 84 registers) took 149; with expf and a full division in
 // the gate 109 (the vector unit bounds it then), with a gate of less than
 // float32's precision 92.
