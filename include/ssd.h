@@ -112,9 +112,10 @@ typedef struct {
  * must be made before the size is asked.  At their other shapes (bf16, those
  * dstates, headdim 64 with a shorter chunk or headdim 128) it covers both; a
  * call there runs on the general kernels where x, B, C or y is not 16-byte
- * aligned or the workspace holds only their layout.  A workspace too small for
- * the path a call takes fails with SSD_ERR_WORKSPACE, never overruns.  Returns SSD_OK
- * and writes *bytes, or a validation error. */
+ * aligned, the workspace holds only their layout, a packed row has fewer than
+ * 24 tokens a sequence, or batch x ngroups exceeds 65535.  A workspace too small
+ * for the path a call takes fails with SSD_ERR_WORKSPACE, never overruns.  Returns
+ * SSD_OK and writes *bytes, or a validation error. */
 int ssd_workspace_bytes(const ssd_problem* prob, size_t* bytes);
 
 /* The SSD forward (Section 6 algorithm; definition above).  `D`,

@@ -1,7 +1,8 @@
 """Calls that the fused kernels take over from the general ones: headdim 128
 (two of their heads a head) and block lengths other than their own, plain and
 packed rows, with the block steps -- and the calls of those shapes that stay on
-the general kernels (operands off 16 bytes, a workspace of the general size).
+the general kernels (operands off 16 bytes, a workspace of the general size,
+packed rows of short sequences, more rows than the fused grid).
 Against the float64 oracle, at the bounds of test_gpu_parity, and, for which
 kernels ran, against the forced general path bit for bit.
 """
